@@ -58,7 +58,7 @@
  * shape (conv_im2win_kernel_name reports which).  Tuning variables in the
  * environment can force another, to measure kernels against each other:
  * IM2WIN_FP16_KERNEL (pipe | regs), IM2WIN_FP16_COL, IM2WIN_FP16_TILE,
- * IM2WIN_FP16_SEG, IM2WIN_FP32_KERNEL (a variant name | regs),
+ * IM2WIN_FP16_SEG, IM2WIN_FP16_DIRECT (a variant name | off), IM2WIN_FP32_KERNEL (a variant name | regs),
  * IM2WIN_FP32_TILE, IM2WIN_FP32_MFMA_TILE (variant names),
  * IM2WIN_TRANSFORM_ORDER and IM2WIN_TILE_ORDER (xcd | linear),
  * IM2WIN_TRANSFORM_KERNEL (pieces | gather: the 3-channel transform),

@@ -446,7 +446,7 @@ int conv16(void *ws, int64_t ws_bytes, const uint16_t *filt_khkwcico, uint16_t *
     const hipStream_t st = (hipStream_t)hip_stream;
     if ((rc = launch_status(launch_pack_fp16(sh, plan, filt_khkwcico, packed, st, split))) != IM2WIN_OK)
         return rc;
-    return launch_status(launch_conv_fp16(sh, plan, tu, ws, packed, out_nhwc, st, op, split));
+    return launch_status(launch_conv_fp16(sh, plan, tu, ws, filt_khkwcico, packed, out_nhwc, st, op, split));
 }
 
 }  // namespace

@@ -271,6 +271,8 @@ int launch_status(hipError_t e);
 //   IM2WIN_FP16_COL        a column-staged variant name
 //   IM2WIN_FP16_TILE       a row-per-pixel tile name (implies pipe)
 //   IM2WIN_FP16_SEG        a segment-staged variant name
+//   IM2WIN_FP16_DIRECT     a small-grid variant name | off (the small-grid
+//                          kernel is not considered)
 //   IM2WIN_FP32_KERNEL     a DMA-staged variant name | regs | stem (short
 //                          unaligned windows, filter from the scalar cache)
 //   IM2WIN_FP32_TILE       a register-staged tile name (implies regs)
@@ -296,7 +298,7 @@ namespace im2win {
 struct Tuning {
     enum { kAuto = 0, kPipe = 1, kRegs = 2, kStem = 3 };
     int fp16_kernel;                   // kAuto, kPipe, kRegs, kStem
-    int fp16_col, fp16_tile, fp16_seg; // variant index, -1: not forced
+    int fp16_col, fp16_tile, fp16_seg, fp16_direct; // variant index, -1: not forced
     int fp32_kernel;                   // DMA variant index, -1: not forced, -2: register-staged kernel,
                                        // -3: short-window kernel
     int fp32_tile;                     // register-staged tile index, -1: not forced
@@ -304,6 +306,7 @@ struct Tuning {
     int fp32_mfma_tile;                // -1: not forced
     bool transform_linear, tile_linear;
     bool transform_gather;             // 3-channel transform: element gather only
+    bool direct_off;                   // the small-grid fp16 kernel is not considered
     bool col_persist;                  // column-staged fp16 kernel: persistent launch where it applies
     enum { kDefault = 0, kLinear = 1, kColumn = 2 };
     int tap_order;  // kDefault: each kernel's own (column for the DMA fp32 kernel, linear for the others)
@@ -321,6 +324,7 @@ constexpr int kMaxSplit = 8;
 int col_find(const char *name);
 int pipe_find(const char *name);
 int seg_find(const char *name);
+int direct_find(const char *name);
 int dma32_find(const char *name);
 int regs32_find(const char *name);
 int mfma32_find(const char *name);
@@ -331,7 +335,7 @@ int mfma32_find(const char *name);
 // layer of N images also runs any layer that differs only in having fewer
 // images (the fit checks do not grow as N shrinks), which the mini-batch
 // path relies on.
-enum class Fam16 { Col, Pipe, Seg, Regs, Stem };
+enum class Fam16 { Col, Pipe, Seg, Regs, Stem, Direct };
 struct Plan16 {
     Fam16 fam;
     int v;       // variant index within the family (Regs: 0..2 tile by C_o)
@@ -412,7 +416,8 @@ enum class Op16 { F16, BF16 };
 hipError_t launch_pack_fp16(const Shape &sh, const Plan16 &p, const uint16_t *filt, void *packed,
                             hipStream_t st, void *split = nullptr);
 hipError_t launch_conv_fp16(const Shape &sh, const Plan16 &p, const Tuning &t, const void *ws,
-                            const void *packed, uint16_t *out, hipStream_t st, Op16 op, void *split = nullptr);
+                            const uint16_t *filt, const void *packed, uint16_t *out, hipStream_t st, Op16 op,
+                            void *split = nullptr);
 // Column-staged fp16 kernel: the default variant for this layer (-1: the
 // row-per-pixel kernels run), whether a variant can run it, its name and
 // taps per stage (the packed-filter tile).
@@ -439,6 +444,14 @@ int stem_default(const Shape &sh);
 const char *stem_name(int v);
 hipError_t launch_conv_fp16_stem(const Shape &sh, int v, const void *ws, const void *packed, uint16_t *out,
                                  hipStream_t st, Op16 op);
+// Small-grid fp16 kernel (taps split over the waves of a workgroup, operands
+// straight to registers, the caller's filter read without a pack): the
+// default variant (-1: another kernel runs), fit, name.
+int direct_default(const Shape &sh);
+bool direct_fits(const Shape &sh, int v);
+const char *direct_name(int v);
+hipError_t launch_conv_fp16_direct(const Shape &sh, int v, const Tuning &t, const void *ws, const uint16_t *filt,
+                                   uint16_t *out, hipStream_t st, Op16 op);
 hipError_t launch_conv_fp16_col(const Shape &sh, int v, const Tuning &t, const void *ws, const void *packed,
                                 uint16_t *out, hipStream_t st, Op16 op);
 // Row-per-pixel fp16 tiles: default for the layer, name, and the K split the

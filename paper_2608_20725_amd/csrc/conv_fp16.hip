@@ -908,6 +908,8 @@ hipError_t launch_pack_fp16(const Shape &sh, const Plan16 &p, const uint16_t *fi
                             void *split)
 {
     (void)split;
+    if (p.fam == Fam16::Direct)
+        return hipSuccess;  // reads the caller's filter
     PackArgs a;
     a.filt = filt;
     a.packed = static_cast<uint16_t *>(packed);
@@ -944,8 +946,11 @@ hipError_t launch_pack_fp16(const Shape &sh, const Plan16 &p, const uint16_t *fi
 }
 
 hipError_t launch_conv_fp16(const Shape &sh, const Plan16 &p, const Tuning &t, const void *ws,
-                            const void *packed, uint16_t *out, hipStream_t st, Op16 op, void *split)
+                            const uint16_t *filt, const void *packed, uint16_t *out, hipStream_t st, Op16 op,
+                            void *split)
 {
+    if (p.fam == Fam16::Direct)
+        return launch_conv_fp16_direct(sh, p.v, t, ws, filt, out, st, op);
     if (p.fam == Fam16::Col)
         return launch_conv_fp16_col(sh, p.v, t, ws, packed, out, st, op);
     if (p.fam == Fam16::Seg)

@@ -12,6 +12,7 @@
 namespace im2win {
 
 typedef float f32x16_acc __attribute__((ext_vector_type(16)));
+typedef float f32x4_acc __attribute__((ext_vector_type(4)));
 
 // fp16 operands (IEEE binary16), v_mfma_f32_32x32x16_f16.
 struct F16Op {
@@ -20,6 +21,10 @@ struct F16Op {
     __device__ static inline f32x16_acc mfma(v8 a, v8 b, f32x16_acc c)
     {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+    }
+    __device__ static inline f32x4_acc mfma16(v8 a, v8 b, f32x4_acc c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
     }
     // fp32 -> fp16 bits, round to nearest even
     __device__ static inline uint32_t bits(float x) { return __builtin_bit_cast(uint16_t, (_Float16)x); }
@@ -32,6 +37,10 @@ struct BF16Op {
     __device__ static inline f32x16_acc mfma(v8 a, v8 b, f32x16_acc c)
     {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+    }
+    __device__ static inline f32x4_acc mfma16(v8 a, v8 b, f32x4_acc c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
     }
     // fp32 -> bf16 bits, round to nearest even (v_cvt_pk_bf16_f32)
     __device__ static inline uint32_t bits(float x) { return __builtin_bit_cast(uint16_t, (__bf16)x); }

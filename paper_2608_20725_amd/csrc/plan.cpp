@@ -64,6 +64,14 @@ int read_tuning(Tuning *t)
         (rc = read_name("IM2WIN_FP32_MFMA_TILE", mfma32_find, &t->fp32_mfma_tile)) != IM2WIN_OK ||
         (rc = read_name("IM2WIN_FP32_COLS", cols32_find, &t->fp32_cols)) != IM2WIN_OK)
         return rc;
+    t->direct_off = false;
+    const char *dv = getenv("IM2WIN_FP16_DIRECT");
+    if (dv && strcmp(dv, "off") == 0) {
+        t->fp16_direct = -1;
+        t->direct_off = true;
+    } else if ((rc = read_name("IM2WIN_FP16_DIRECT", direct_find, &t->fp16_direct)) != IM2WIN_OK) {
+        return rc;
+    }
     const char *e = getenv("IM2WIN_FP32_KERNEL");
     if (e && strcmp(e, "regs") == 0)
         t->fp32_kernel = -2;
@@ -109,7 +117,7 @@ int read_tuning(Tuning *t)
     }
     // contradictory choices
     const int fam16 = (t->fp16_col >= 0) + (t->fp16_seg >= 0) + (t->fp16_tile >= 0 || t->fp16_kernel == Tuning::kPipe) +
-                      (t->fp16_kernel == Tuning::kRegs) + (t->fp16_kernel == Tuning::kStem);
+                      (t->fp16_kernel == Tuning::kRegs) + (t->fp16_kernel == Tuning::kStem) + (t->fp16_direct >= 0);
     if (fam16 > 1)
         return IM2WIN_EINVAL;
     if ((t->fp32_tile >= 0) + (t->fp32_kernel >= 0 || t->fp32_kernel == -3 || t->fp32_kernel == -2) +
@@ -122,7 +130,8 @@ Tuning default_tuning()
 {
     Tuning t;
     t.fp16_kernel = Tuning::kAuto;
-    t.fp16_col = t.fp16_tile = t.fp16_seg = -1;
+    t.fp16_col = t.fp16_tile = t.fp16_seg = t.fp16_direct = -1;
+    t.direct_off = false;
     t.fp32_kernel = t.fp32_tile = t.fp32_mfma_tile = t.fp32_cols = -1;
     t.transform_linear = t.tile_linear = false;
     t.transform_gather = false;
@@ -191,6 +200,12 @@ int plan_fp16_family(const Shape &sh, const Tuning &t, Plan16 *p)
         *p = Plan16{Fam16::Stem, v};
         return IM2WIN_OK;
     }
+    if (t.fp16_direct >= 0) {
+        if (!direct_fits(sh, t.fp16_direct))
+            return IM2WIN_EINVAL;
+        *p = Plan16{Fam16::Direct, t.fp16_direct};
+        return IM2WIN_OK;
+    }
     if (t.fp16_col >= 0) {
         if (!col_fits(sh, t.fp16_col))
             return IM2WIN_EINVAL;
@@ -207,6 +222,11 @@ int plan_fp16_family(const Shape &sh, const Tuning &t, Plan16 *p)
         if (!aligned)
             return IM2WIN_EINVAL;
         *p = Plan16{Fam16::Pipe, t.fp16_tile >= 0 ? t.fp16_tile : pipe_default(sh)};
+        return IM2WIN_OK;
+    }
+    const int dr = t.direct_off ? -1 : direct_default(sh);
+    if (dr >= 0) {
+        *p = Plan16{Fam16::Direct, dr};
         return IM2WIN_OK;
     }
     if (aligned) {
@@ -298,6 +318,7 @@ void plan16_name(const Shape &sh, const Plan16 &p, char *buf, int len)
             snprintf(buf, len, "conv_fp16_pipe %s", pipe_name(p.v));
         break;
     case Fam16::Seg: snprintf(buf, len, "conv_fp16_seg %s", seg_name(p.v)); break;
+    case Fam16::Direct: snprintf(buf, len, "conv_fp16_direct %s", direct_name(p.v)); break;
     case Fam16::Stem: snprintf(buf, len, "conv_fp16_stem %s", stem_name(p.v)); break;
     case Fam16::Regs: {
         static const char *tiles[] = {"c32p256", "c64p256", "c128p128"};
