@@ -61,7 +61,7 @@
  * IM2WIN_FP16_SEG, IM2WIN_FP16_DIRECT (a variant name | off), IM2WIN_FP32_KERNEL (a variant name | regs),
  * IM2WIN_FP32_TILE, IM2WIN_FP32_MFMA_TILE (variant names),
  * IM2WIN_TRANSFORM_ORDER and IM2WIN_TILE_ORDER (xcd | linear),
- * IM2WIN_TRANSFORM_KERNEL (pieces | gather: the 3-channel transform),
+ * IM2WIN_TRANSFORM_KERNEL (pieces | gather: the transform of windows not 16-byte aligned),
  * IM2WIN_FP16_PERSIST (on | off: the column-staged kernel's persistent launch),
  * IM2WIN_TAP_ORDER (linear | column: the filter columns' tap slices in turn,
  * the columns grouped by residue mod the stride), IM2WIN_FP16_SPLIT (1..8: the K range

@@ -282,9 +282,9 @@ int launch_status(hipError_t e);
 //   IM2WIN_FP16_PERSIST    on | off: column-staged fp16 kernel in one round of
 //                          workgroups that walk the tiles (on by default
 //                          where it applies) or one workgroup per tile
-//   IM2WIN_TRANSFORM_KERNEL pieces | gather: the 3-channel layers' transform
-//                          (one load per 3-channel pixel, where it is the
-//                          faster, or one per element)
+//   IM2WIN_TRANSFORM_KERNEL pieces | gather: the transform of layers whose
+//                          C_i*elt is not a multiple of 16 bytes (pieces put
+//                          together in LDS, or element by element)
 //   IM2WIN_TILE_ORDER      linear | xcd
 //   IM2WIN_TAP_ORDER       linear | column: the K-loop order of the DMA-staged
 //                          fp32 kernel (column by default) and of the
@@ -305,7 +305,8 @@ struct Tuning {
     int fp32_cols;                     // column-staged variant index, -1: not forced
     int fp32_mfma_tile;                // -1: not forced
     bool transform_linear, tile_linear;
-    bool transform_gather;             // 3-channel transform: element gather only
+    bool transform_gather;             // unaligned C_i: element gather only
+    bool transform_pieces;             // unaligned C_i: LDS-assembled pieces wherever they can run
     bool direct_off;                   // the small-grid fp16 kernel is not considered
     bool col_persist;                  // column-staged fp16 kernel: persistent launch where it applies
     enum { kDefault = 0, kLinear = 1, kColumn = 2 };

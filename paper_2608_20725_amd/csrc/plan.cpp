@@ -89,11 +89,13 @@ int read_tuning(Tuning *t)
         else if (*e && strcmp(e, "on") != 0)
             return IM2WIN_EINVAL;
     }
-    t->transform_gather = false;
+    t->transform_gather = t->transform_pieces = false;
     if (const char *e = getenv("IM2WIN_TRANSFORM_KERNEL")) {
         if (strcmp(e, "gather") == 0)
             t->transform_gather = true;
-        else if (*e && strcmp(e, "pieces") != 0)
+        else if (strcmp(e, "pieces") == 0)
+            t->transform_pieces = true;
+        else if (*e)
             return IM2WIN_EINVAL;
     }
     t->tap_order = Tuning::kDefault;
@@ -134,7 +136,7 @@ Tuning default_tuning()
     t.direct_off = false;
     t.fp32_kernel = t.fp32_tile = t.fp32_mfma_tile = t.fp32_cols = -1;
     t.transform_linear = t.tile_linear = false;
-    t.transform_gather = false;
+    t.transform_gather = t.transform_pieces = false;
     t.col_persist = true;
     t.tap_order = Tuning::kDefault;
     t.fp16_split = 0;

@@ -9,12 +9,12 @@
 //             16-byte granules; a workgroup covers a contiguous run of the
 //             window tensor (possibly across strips), so the stores of a wave
 //             are one contiguous 1 KiB run, in an XCD-aware block order.
-//   * gather: any other C_i.  A thread assembles one 16-byte granule of the
-//             flat window tensor element by element; granules may straddle
-//             strips.
-//   * pieces3: the gather for C_i = 3 (the stem layers), undilated and
-//             unpadded (fp32; fp16 with K_h <= 3), reading each 3-channel
-//             pixel it needs with one load.
+//   * pieces: any other C_i, undilated: a workgroup reads the input rows of
+//             a piece of the window tensor in their own order and puts the
+//             piece together in LDS.
+//   * gather: the rest (dilated layers, very small ones).  A thread assembles
+//             one 16-byte granule of the flat window tensor element by
+//             element; granules may straddle strips.
 // All zero the pad bytes that follow the window tensor.
 //
 // Zero padding of the input (not in the paper's layers) is folded in: the
@@ -44,9 +44,11 @@ struct TArgs {
     uint64_t win_elems;
     uint64_t win_bytes, pad_end;
     uint64_t grans;          // gather: 16-byte granules of the window tensor
-    uint64_t in_pixels;      // pieces3: pixels of the input (N * H_i * W_i)
-    uint32_t xcd_order;      // vec: 1 = XCD-aware block order, 0 = linear (ablation)
-    FastDiv div_Ci, div_Kh, div_Wi, div_Ho, div_L, div_gps, div_Wq;
+    uint64_t in_pixels;      // pieces: pixels of the input (N * H_i * W_i)
+    uint32_t cu;             // pieces: units per pixel
+    uint32_t spb, segs, cpb; // pieces: strips per block; pieces per strip, columns per piece
+    uint32_t xcd_order;      // vec, pieces: 1 = XCD-aware block order, 0 = linear (ablation)
+    FastDiv div_Ci, div_Kh, div_Wi, div_Ho, div_L, div_gps, div_Wq, div_cu;
 };
 
 // Padded-input column held by strip column position k: k itself, or with
@@ -117,89 +119,163 @@ __global__ __launch_bounds__(kThreads) void transform_vec(TArgs a)
     }
 }
 
-template <int ELT>
-__device__ inline void store_elem_t(uint32_t *w, int e, uint32_t bits)
-{
-    if (ELT == 4) {
-        w[e] = bits;
-    } else {
-        const int d = e >> 1;
-        w[d] = (e & 1) ? (w[d] & 0xffffu) | (bits << 16) : (w[d] & 0xffff0000u) | (bits & 0xffffu);
-    }
-}
+// Strips of any other C_i, undilated: what bounds the element gather below is
+// not memory but the order of its reads, a granule's elements lying in up to
+// eight input rows, and the index arithmetic of every element.  Here a
+// workgroup owns a contiguous piece of the window tensor of at most 16 KiB
+// (some columns of a strip, or a few whole strips), reads the input rows it
+// comes from in their own order, places each element in LDS where the window
+// tensor has it, and copies the piece out as 16-byte granules.  A row's
+// position (image, strip, filter row) is the same for a whole wave, so a lane
+// adds little more than one LDS address per element.  Measured (us, 128
+// images unless said, element gather -> pieces): fp16 11x11 stride 4 at
+// 227x227 65 -> 40, 7x7 stride 2 80 -> 49, 3x3 at 224x224 64 -> 42; fp32 7x7
+// stride 2 pad 3 at 224x224, 32 images, 27.4 -> 18.6 (4.8 TB/s), 11x11 74 ->
+// 58; fp16 3x3 52 channels at 81x81, 92 images, 108 -> 38; and against the
+// one-load-per-pixel gather it replaces, fp32 3x3 at 224x224 67 -> 60.
+//
+// The row is read as units of UB = 2, 4 or 8 bytes, the largest that divides
+// a pixel's C_i*elt bytes, V consecutive units per lane and load: 16 bytes (8
+// with 2-byte units), one unit for rows too short to fill a wave that way, or
+// three: one 3-channel pixel, which needs no carry into the next column.  Padding rows and columns are the zeros the piece starts
+// with.
+template <int UB>
+struct UnitOf;
+template <>
+struct UnitOf<2> { typedef uint16_t type; };
+template <>
+struct UnitOf<4> { typedef uint32_t type; };
+template <>
+struct UnitOf<8> { typedef uint64_t type; };
 
-// The gather of the 3-channel layers with one load per piece: a 16-byte
-// granule of the window tensor (8 fp16 or 4 fp32 elements) spans at most 4
-// (fp16) or 2 (fp32) pieces, a piece being the 3 channels of one input pixel
-// (one column of one filter row of one strip).  Each piece is read with one
-// load, 8 bytes for fp16 (6 used) and 12 for fp32, instead of one load per
-// element; the granule is assembled in registers and stored whole, so a
-// wave's stores stay one contiguous 1 KiB run.  An 8-byte fp16 read would
-// reach 2 bytes past the last pixel of the input: that piece is read as 4 + 2
-// bytes.
-template <int ELT>
-__global__ __launch_bounds__(kThreads) void transform_pieces3(TArgs a)
+constexpr uint32_t kPieceBytes = 16384;
+
+template <int UB, int V>
+__global__ __launch_bounds__(kThreads) void transform_pieces(TArgs a)
 {
-    constexpr uint32_t V = 16 / ELT;                // elements per granule
-    constexpr int NP = ELT == 2 ? 4 : 2;            // pieces a granule can touch
-    const uint64_t g = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
+    typedef typename UnitOf<UB>::type unit;
+    constexpr int U = 4;  // loads in flight per lane
+    __shared__ uint4 buf[kPieceBytes / 16 + 2];
+    char *lds = reinterpret_cast<char *>(buf);
+
     if (blockIdx.x == 0)
         zero_pad(a);
-    if (g >= a.grans)
-        return;
-    // first element of this granule (win_elems < 2^32, checked on the host)
-    const uint32_t e0 = (uint32_t)(g * V);
-    uint32_t q = fdiv(e0, a.div_L);
-    const uint32_t pos = e0 - q * a.L;
-    uint32_t seg = fdiv(pos, a.div_Ci);              // k*K_h + u of the first piece
-    const uint32_t r0 = pos - seg * 3;               // its first channel used
-    const uint32_t segs = a.L / 3;                   // pieces per strip (W_i * K_h)
-    uint32_t el[NP * 3];                             // the pieces' elements (ELT bytes each)
-#pragma unroll
-    for (int j = 0; j < NP; ++j) {
-        el[3 * j] = el[3 * j + 1] = el[3 * j + 2] = 0u;
-        // piece j holds granule elements 3j - r0 .. 3j - r0 + 2
-        if (3 * j >= (int)(r0 + V) || (uint64_t)e0 + 3 * j - r0 >= a.win_elems)
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t b = a.xcd_order ? xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
+    const uint32_t sb = b / a.segs, seg = b - sb * a.segs;
+    const uint32_t q0 = sb * a.spb;                                      // first strip
+    const uint32_t ns = a.strips - q0 < a.spb ? a.strips - q0 : a.spb;   // strips (1 if a strip is split)
+    const uint32_t k0 = seg * a.cpb;                                     // first column
+    const uint32_t k1 = a.Wp - k0 < a.cpb ? a.Wp : k0 + a.cpb;
+    const uint32_t cu = a.cu, colu = a.Kh * cu;                          // units per pixel and per column
+    const uint32_t stripu = a.Wp * colu;                                 // units per strip
+    const uint64_t first = ((uint64_t)q0 * stripu + (uint64_t)k0 * colu) * UB;  // byte offset of the piece
+    const uint32_t len = (ns > 1 ? ns * stripu : (k1 - k0) * colu) * UB;
+    const uint32_t lead = (uint32_t)first & 15u;                         // its offset in its first granule
+
+    if (a.ph | a.pw) {
+        for (uint32_t g = threadIdx.x; g < kPieceBytes / 16 + 2; g += kThreads)
+            buf[g] = make_uint4(0u, 0u, 0u, 0u);
+        __syncthreads();
+    }
+    // stored columns among k0 .. k1-1
+    const uint32_t v0 = k0 > a.pw ? k0 : a.pw, v1 = k1 < a.pw + a.Wi ? k1 : a.pw + a.Wi;
+    const uint32_t rows = v0 < v1 ? ns * a.Kh : 0u, n = v0 < v1 ? (v1 - v0) * cu : 0u;
+    for (uint32_t rr = wave; rr < rows; rr += kThreads / 64) {
+        const uint32_t st = fdiv(rr, a.div_Kh), u = rr - st * a.Kh;
+        const uint32_t q = q0 + st, i = fdiv(q, a.div_Ho), m = q - i * a.Ho;
+        const int32_t h = (int32_t)(m * a.s + u) - (int32_t)a.ph;
+        if (h < 0 || h >= (int32_t)a.Hi)
             continue;
-        if (seg == segs) {  // into the next strip
-            seg = 0;
-            ++q;
-        }
-        const uint32_t k = fdiv(seg, a.div_Kh), u = seg - k * a.Kh;
-        const uint32_t i = fdiv(q, a.div_Ho), m = q - i * a.Ho;
-        const uint64_t px = ((uint64_t)i * a.Hi + m * a.s + u) * a.Wi + k;  // input pixel
-        const char *src = a.in + px * (3 * ELT);
-        if (ELT == 4) {
-            uint32_t v[3];
-            __builtin_memcpy(v, src, 12);
-            el[3 * j] = v[0]; el[3 * j + 1] = v[1]; el[3 * j + 2] = v[2];
-        } else {
-            uint64_t v;  // one 8-byte load (the last pixel: 4 + 2 bytes)
-            if (px + 1 < a.in_pixels) {
-                __builtin_memcpy(&v, src, 8);
-            } else {
-                uint32_t lo;
-                uint16_t hi;
-                __builtin_memcpy(&lo, src, 4);
-                __builtin_memcpy(&hi, src + 4, 2);
-                v = lo | ((uint64_t)hi << 32);
-            }
-            el[3 * j] = (uint32_t)v & 0xffffu;
-            el[3 * j + 1] = (uint32_t)(v >> 16) & 0xffffu;
-            el[3 * j + 2] = (uint32_t)(v >> 32) & 0xffffu;
-        }
-        ++seg;
-    }
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
+        const uint64_t px = ((uint64_t)i * a.Hi + (uint32_t)h) * a.Wi + (v0 - a.pw);
+        const char *src = a.in + px * cu * UB;
+        char *dst = lds + lead + (st * stripu + ((v0 - k0) * a.Kh + u) * cu) * UB;
+        if constexpr (V == 3) {
+            // the last row of the input: its last pixel's 8-byte load starts 2 bytes early
+            const bool end = UB == 2 && px + (v1 - v0) == a.in_pixels;
+            const uint32_t nk = v1 - v0;
+            for (uint32_t x = lane; x < nk; x += 64 * U) {
+                unit el[U][3];
 #pragma unroll
-    for (uint32_t t = 0; t < V; ++t) {
-        // element t of the granule is element r0 + t of the pieces' run
-        // (r0 < 3)
-        const uint32_t bits = r0 == 0 ? el[t] : r0 == 1 ? el[t + 1] : el[t + 2];
-        store_elem_t<ELT>(w, (int)t, bits);
+                for (int t = 0; t < U; ++t) {
+                    if constexpr (UB == 2) {
+                        // lanes past the row repeat its last pixel (a branch
+                        // per load measured 44.0 vs 41.0 us on 11x11 stride 4)
+                        const uint32_t k = x + 64 * t < nk ? x + 64 * t : nk - 1;
+                        const uint32_t adj = end && k == nk - 1 ? 2u : 0u;
+                        uint32_t v[2];
+                        __builtin_memcpy(v, src + (int32_t)(k * 6u - adj), 8);  // -2 for a row's only pixel
+                        if (end) {
+                            v[0] = adj ? __builtin_amdgcn_alignbyte(v[1], v[0], 2) : v[0];
+                            v[1] = adj ? v[1] >> 16 : v[1];
+                        }
+                        el[t][0] = (unit)v[0];
+                        el[t][1] = (unit)(v[0] >> 16);
+                        el[t][2] = (unit)v[1];
+                    } else if (x + 64 * t < nk) {
+                        __builtin_memcpy(el[t], src + (x + 64 * t) * 12u, 12);
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < U; ++t) {
+                    uint32_t k = x + 64 * t;
+                    if (UB == 2)
+                        k = k < nk ? k : nk - 1;
+                    else if (k >= nk)
+                        continue;
+                    unit *o = reinterpret_cast<unit *>(dst + k * (colu * UB));
+                    o[0] = el[t][0];
+                    o[1] = el[t][1];
+                    o[2] = el[t][2];
+                }
+            }
+        } else {
+            // whole groups of V units, then the row's last n % V
+            for (uint32_t x = lane * V; x + V <= n; x += 64 * V * U) {
+                unit el[U][V];
+#pragma unroll
+                for (int t = 0; t < U; ++t)
+                    if (x + 64 * V * t + V <= n)
+                        __builtin_memcpy(el[t], src + (x + 64 * V * t) * UB, V * UB);
+#pragma unroll
+                for (int t = 0; t < U; ++t) {
+                    const uint32_t xt = x + 64 * V * t;
+                    if (xt + V > n)
+                        continue;
+                    const uint32_t k = fdiv(xt, a.div_cu);
+                    uint32_t r = xt - k * cu, o = (k * colu + r) * UB;
+#pragma unroll
+                    for (int e = 0; e < V; ++e) {
+                        *reinterpret_cast<unit *>(dst + o) = el[t][e];
+                        const bool wrap = ++r == cu;  // into the next column
+                        o += wrap ? UB + (colu - cu) * UB : UB;
+                        r = wrap ? 0u : r;
+                    }
+                }
+            }
+            const uint32_t xt = n - n % V + lane;
+            if (V > 1 && xt < n) {
+                unit el;
+                __builtin_memcpy(&el, src + xt * UB, UB);
+                const uint32_t k = fdiv(xt, a.div_cu);
+                *reinterpret_cast<unit *>(dst + (k * colu + (xt - k * cu)) * UB) = el;
+            }
+        }
     }
-    // bytes past the window tensor are inside the zero pad: zeros are written
-    *reinterpret_cast<uint4 *>(a.ws + g * 16) = make_uint4(w[0], w[1], w[2], w[3]);
+    __syncthreads();
+    // whole granules, and the elements of the first and last one that this
+    // piece shares with its neighbours
+    char *out = a.ws + (first - lead);
+    for (uint32_t g = threadIdx.x; 16 * g < lead + len; g += kThreads) {
+        if (16 * g >= lead && 16 * g + 16 <= lead + len) {
+            *reinterpret_cast<uint4 *>(out + 16 * (uint64_t)g) = buf[g];
+        } else {
+            for (uint32_t o = 16 * g; o < 16 * g + 16; o += UB)
+                if (o >= lead && o < lead + len)
+                    *reinterpret_cast<unit *>(out + o) = *reinterpret_cast<const unit *>(lds + o);
+        }
+    }
 }
 
 template <int ELT>
@@ -327,18 +403,57 @@ hipError_t launch_transform(const Shape &sh, const void *in, void *ws, hipStream
     const uint64_t blocks = (a.grans + kThreads - 1) / kThreads;
     if (blocks > 0x7fffffffull)
         return hipErrorInvalidValue;
-    // pieces3: 3-channel layers, undilated and unpadded; in fp16 only with
-    // filters of up to 3 rows.  Measured against the element gather (GB/s of
-    // algorithmic traffic, 128 images): fp32 11x11 stride 4 at 227x227 4512
-    // against 4059, 7x7 stride 2 3925 / 3180, 3x3 at 224x224 4277 / 3996;
-    // fp16 3x3 2613 / 2376, 7x7 even, 11x11 2135 / 2298 (a granule's pieces
-    // then come from up to four input rows).  IM2WIN_TRANSFORM_KERNEL=gather
-    // keeps every layer on the element gather.
-    const bool unpadded = !pad || (pad->ph == 0 && pad->pw == 0);
-    if (sh.Ci == 3 && sh.d == 1 && unpadded && !t.transform_gather && (sh.elt == 4 || sh.Kh <= 3)) {
-        a.in_pixels = (uint64_t)sh.N * a.Hi * a.Wi;
-        const void *f = sh.elt == 4 ? (const void *)&transform_pieces3<4> : (const void *)&transform_pieces3<2>;
-        return hipLaunchKernel(f, dim3((uint32_t)blocks), dim3(kThreads), args, 0, st);
+    // pieces: undilated layers whose columns leave room for two in a piece,
+    // where the window tensor is large enough to repay the second pass
+    // through LDS: 16-bit from 512 KiB on (3x5 36 channels, 1.0 MB: 3.5 vs
+    // 4.3 us; 7x7 3-channel, 1.1 MB: even), fp32, with half the elements per
+    // granule, from 4 MiB (7x7 3-channel, 2.1 MB: 4.4 vs 3.8; 3x3 30
+    // channels, 9.3 MB: 5.7 vs 6.1).  One-row filters, whose gather reads in
+    // input order, from 4 MiB and more than 3 channels (1x1 100 channels
+    // fp16, 20 MB: 8.0 vs 15.2; 141 channels fp32, 2.7 MB: 4.9 vs 3.8; 3
+    // channels fp16, 4.8 MB: 7.0 vs 6.2); one and two channels stay with the
+    // gather (5x5 one channel, 32 MB: 11.3 vs 8.9).
+    // IM2WIN_TRANSFORM_KERNEL=pieces takes it wherever it can run, =gather
+    // nowhere.
+    const int64_t colb = sh.Kh * sh.Ci * sh.elt;
+    a.in_pixels = (uint64_t)sh.N * a.Hi * a.Wi;
+    if (sh.d == 1 && 2 * colb <= kPieceBytes && a.in_pixels > 1 && !t.transform_gather &&
+        (t.transform_pieces || (sh.Ci > (sh.Kh > 1 ? 2 : 3) &&
+                                (int64_t)a.grans >= (sh.elt == 4 || sh.Kh == 1 ? 1 << 18 : 1 << 15)))) {
+        // pieces of at most 16 KiB (eight blocks per CU), smaller ones while
+        // there is less than one per CU (512 or 1024 pieces measured up to
+        // 1.1 us slower on single images, even on large batches)
+        const int64_t most = kPieceBytes / colb, want = 256;
+        int64_t cpb = sh.Wi < most ? sh.Wi : most, spb = 1;
+        if (cpb < sh.Wi || sh.strips < want) {
+            int64_t segs = (sh.Wi + cpb - 1) / cpb;
+            if (sh.strips * segs < want)
+                segs = (want + sh.strips - 1) / sh.strips;
+            cpb = (sh.Wi + segs - 1) / segs;
+            cpb = cpb < 4 ? (sh.Wi < 4 ? sh.Wi : 4) : cpb;
+            cpb = cpb < most ? cpb : most;
+        } else {
+            spb = kPieceBytes / (sh.Wi * colb);
+            const int64_t lim = sh.strips / want;
+            spb = spb < lim ? spb : lim;
+            spb = spb < 1 ? 1 : spb;
+        }
+        a.cpb = (uint32_t)cpb;
+        a.spb = (uint32_t)spb;
+        a.segs = (uint32_t)((sh.Wi + cpb - 1) / cpb);
+        const int64_t nb = (sh.strips + spb - 1) / spb * a.segs;
+        const int64_t pxb = sh.Ci * sh.elt;
+        const int ub = pxb % 8 == 0 ? 8 : pxb % 4 == 0 && sh.Ci != 3 ? 4 : (int)sh.elt;
+        a.cu = (uint32_t)(pxb / ub);
+        a.div_cu = make_fastdiv(a.cu);
+        const bool narrow = cpb * a.cu <= 256;  // one unit per lane, U times, covers a row
+        const void *f =
+            sh.Ci == 3 ? (sh.elt == 4 ? (const void *)&transform_pieces<4, 3> : (const void *)&transform_pieces<2, 3>)
+            : ub == 8  ? (narrow ? (const void *)&transform_pieces<8, 1> : (const void *)&transform_pieces<8, 2>)
+            : ub == 4  ? (narrow ? (const void *)&transform_pieces<4, 1> : (const void *)&transform_pieces<4, 4>)
+                       : (narrow ? (const void *)&transform_pieces<2, 1> : (const void *)&transform_pieces<2, 4>);
+        if (nb <= 0x7fffffff)
+            return hipLaunchKernel(f, dim3((uint32_t)nb), dim3(kThreads), args, 0, st);
     }
     // gather: element indices fit 32 bits (transform_range_ok)
     const void *f = sh.elt == 4 ? (const void *)&transform_gather<4> : (const void *)&transform_gather<2>;

@@ -136,3 +136,28 @@ def test_transform_unaligned(shape, dtype):
     x, w = workloads.draw(N, Ci, H, W, 2, Kh, Kw, seed=5 + sum(shape))
     run = Run(x, w, s, dtype, conv=False)
     _compare(run, x)
+
+
+# The pieces kernel where its units, loads and pieces end: 2-, 4- and 8-byte
+# units, rows shorter than one load and rows of several rounds, split strips
+# and several strips per piece, padding on one side only reaching some pieces,
+# against the element gather (itself compared with the oracle above).
+@pytest.mark.parametrize("dtype", DTYPES, ids=["f32", "f16", "bf16"])
+@pytest.mark.parametrize("case", [
+    (1, 5, 3, 2, 3, 1, 1, 0, 0), (2, 7, 9, 300, 3, 1, 1, 0, 0), (2, 6, 40, 9, 3, 2, 1, 1, 2),
+    (3, 12, 9, 130, 5, 3, 2, 2, 0), (1, 141, 12, 37, 3, 1, 1, 0, 3), (300, 3, 8, 8, 3, 1, 1, 1, 1),
+    (2, 3, 9, 400, 7, 2, 1, 3, 3), (1, 3, 4, 1, 2, 1, 1, 0, 0), (1, 3, 2, 2, 1, 1, 1, 5, 4), (2, 260, 9, 9, 7, 1, 1, 0, 1),
+], ids=lambda s: "x".join(map(str, s)))
+def test_transform_pieces_equal_gather(case, dtype, monkeypatch):
+    import paper_2608_20725_amd as pkg
+    N, Ci, H, W, Kh, s, Kw, ph, pw = case
+    x, _ = workloads.draw(N, Ci, H, W, 2, Kh, Kw, seed=31 + sum(case))
+    xd = x.to(dtype).cuda()
+    need = pkg.conv_workspace_bytes(N, Ci, H + 2 * ph, W + 2 * pw, 2, Kh, Kw, s, dtype)
+    outs = []
+    for kernel in ("pieces", "gather"):
+        monkeypatch.setenv("IM2WIN_TRANSFORM_KERNEL", kernel)
+        ws = torch.full((need + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        pkg.conv_im2win_transform_padded(xd, ws[:need], 2, Kh, Kw, s, ph, pw)
+        outs.append(ws.cpu())
+    assert torch.equal(outs[0], outs[1])
