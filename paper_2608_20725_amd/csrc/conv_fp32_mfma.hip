@@ -43,6 +43,7 @@ struct M32Args {
     WinCols wc;
     TileGrid tg;          // pixel x channel tiles of the 1-D launch
     FastDiv div_Wo;
+    TapOrder to;          // order of the 32-tap stages
 };
 
 // Filter repack: element (tile, j, t) = F'[j][tile*32 + t] with
@@ -111,18 +112,21 @@ struct MTile {
     uint32_t voff[C::I];    // byte offset of this lane's chunk at tap 0 (kOOB: no pixel)
     uint32_t vtap[C::I];    // first tap of this lane's chunk within a stage
     uint32_t wave, lane, K, nst, apitch, arow, brow;
+    TapOrder to;
     floatx16 acc[C::WM][C::WN];
 
     // Stage s >= nst loads nothing (zero-filled).
     __device__ inline void issue(uint32_t st, char *slot)
     {
-        const uint32_t k0 = st * BK;
+        // first tap of the stage (column order only when every stage is
+        // whole), which is filter tile k0 / 32
+        const uint32_t k0 = to.map(st * BK), fadd = k0 / BK * apitch;
         const bool past = st >= nst;
 #pragma unroll
         for (int j = 0; j < C::I; ++j) {
             const uint32_t b = wave + C::NW * j;
             const bool filt = b < (uint32_t)C::BM / 8;
-            uint32_t off = voff[j] + (filt ? st * apitch : 4u * k0);
+            uint32_t off = voff[j] + (filt ? fadd : 4u * k0);
             if (past || (!filt && k0 + vtap[j] >= K))
                 off = kOOB;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(filt ? rf : rw, (lds_ptr)(slot + 1024 * b), 16, off, 0, 0, 0);
@@ -186,7 +190,13 @@ __global__ __launch_bounds__(C::NT) void conv_fp32_mfma(M32Args a)
     __shared__ __attribute__((aligned(1024))) char r0[C::STAGE];
     __shared__ __attribute__((aligned(1024))) char r1[C::STAGE];
     __shared__ __attribute__((aligned(1024))) char r2[S2];
-    __shared__ uint32_t rowoff[C::BN];
+    // Window offsets of the tile's pixels, in the slot that is loaded last (the
+    // first load into it follows a barrier that follows every read of them):
+    // an array of its own would take the 64 x 256 tile past half of the
+    // 160 KiB LDS, one workgroup per CU instead of two (7x7 C=64 stride 2 at
+    // 224x224: 5204 us vs 4761 together
+    // with the column order of launch_conv_fp32_mfma).
+    uint32_t *const rowoff = reinterpret_cast<uint32_t *>(C::NS > 2 ? r2 : r1);
 
     MTile<C> w;
     const uint32_t tid = threadIdx.x;
@@ -194,6 +204,7 @@ __global__ __launch_bounds__(C::NT) void conv_fp32_mfma(M32Args a)
     w.wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     __builtin_assume(w.wave < (uint32_t)C::NW);
     w.K = a.K;
+    w.to = a.to;
     w.nst = a.K_pad / BK;
     const uint32_t wm = w.wave / C::WGN, wn = w.wave % C::WGN;
     uint32_t tx, ty;
@@ -358,15 +369,29 @@ int mfma32_default(const Shape &sh)
 {
     int n;
     const MVariant *v = m_variants(&n);
-    // The largest tile whose grid gives every CU two workgroups (512), else
-    // the one with the most workgroups: on few-pixel layers the matrix cores
-    // otherwise sit idle (3x3 C=512 at 7x7: 100 tiles of 128 x 128).
-    auto tiles = [&](const MVariant &t) { return ((sh.P + t.bn - 1) / t.bn) * ((sh.Co + t.bm - 1) / t.bm); };
-    if (sh.Co <= 32)
-        return 2;
-    if (sh.Co <= 64)
-        return tiles(v[1]) >= 512 ? 1 : 3;
-    return tiles(v[0]) >= 512 ? 0 : tiles(v[3]) >= 512 ? 3 : 4;
+    // The matrix cores bound these tiles, and a CU's workgroups share them:
+    // the time is that of the CU with the most tiles, ceil(tiles / 256) tiles
+    // of bm x bn sums, times what the tile's operand reads cost beside a
+    // 128 x 128 one's (3x3 64 -> 128 at 112x112, 6050 tiles: 1826 us; 64-row
+    // tiles 1880, 32 x 128 1977, 32 x 256 2031).  Against the largest tile
+    // with two workgroups per CU: 3x3 C=512 at 14x14 (576 / 2304 tiles) 848 ->
+    // 713 us, 3x3 C=256 at 14x14 226 -> 207, 1x1 C=1024 at 14x14 457 -> 437.
+    static const int weight[] = {100, 103, 111, 103, 108};  // by variant
+    int best = 0;
+    int64_t least = -1;
+    for (int i = 0; i < n; ++i) {
+        const int64_t tiles = ((sh.P + v[i].bn - 1) / v[i].bn) * ((sh.Co + v[i].bm - 1) / v[i].bm);
+        // one workgroup per CU leaves its barriers and load waits uncovered
+        // (1x1 140 -> 313 at 18x18, 15 images: 190 tiles 17.7 us, 380 half as
+        // large 16.2)
+        const int64_t alone = tiles <= 256 ? 106 : 100;
+        const int64_t cost = (tiles + 255) / 256 * v[i].bm * v[i].bn * weight[i] * alone;
+        if (least < 0 || cost < least) {
+            best = i;
+            least = cost;
+        }
+    }
+    return best;
 }
 
 hipError_t launch_conv_fp32_mfma(const Shape &sh, const Plan32 &plan, const Tuning &t, const float *filt,
@@ -403,6 +428,13 @@ hipError_t launch_conv_fp32_mfma(const Shape &sh, const Plan32 &plan, const Tuni
     a.Wo = (uint32_t)sh.Wo; a.L = (uint32_t)sh.L;
     a.wc = make_wincols(sh);
     a.div_Wo = make_fastdiv((uint32_t)sh.Wo);
+    // Column order where windows overlap with a stride: 7x7 stride 2 C=64 at
+    // 224x224 is bound by re-reading its windows in linear order, 5405 us
+    // against 4761.  At stride 1 linear order is ahead: 3x3 C=64 at 56x56
+    // 253 against 266, 3x3 C=512 at 7x7 177 against 192, 3x3 64 -> 128 at
+    // 112x112 1770 against 1800.
+    const bool linear = t.tap_order == Tuning::kDefault ? sh.s == 1 || sh.Kw <= sh.s : t.tap_order == Tuning::kLinear;
+    a.to = make_taporder(sh.Kw, sh.Kh, sh.Ci, (uint32_t)BK, linear, sh.s);
     const int64_t gx = (sh.P + v[pick].bn - 1) / v[pick].bn, gy = (sh.Co + v[pick].bm - 1) / v[pick].bm;
     if (gx * gy > 0x7fffffff)
         return hipErrorInvalidValue;
