@@ -106,28 +106,47 @@ def conv_im2win_strerror(status: int) -> str:
     return load_library().conv_im2win_strerror(int(status)).decode()
 
 
+_codes = None
+
+
 def _dtype_code(dtype) -> int:
-    import torch
-    if dtype in (F32, "f32", "fp32", torch.float32):
-        return F32
-    if dtype in (F16, "f16", "fp16", torch.float16):
-        return F16
-    if dtype in (BF16, "bf16", torch.bfloat16):
-        return BF16
-    raise ValueError("dtype must be fp32, fp16 or bf16, got %r" % (dtype,))
+    global _codes
+    if _codes is None:
+        import torch
+        _codes = {F32: F32, "f32": F32, "fp32": F32, torch.float32: F32,
+                  F16: F16, "f16": F16, "fp16": F16, torch.float16: F16,
+                  BF16: BF16, "bf16": BF16, torch.bfloat16: BF16}
+    try:
+        return _codes[dtype]
+    except (KeyError, TypeError):
+        raise ValueError("dtype must be fp32, fp16 or bf16, got %r" % (dtype,)) from None
+
+
+_raw_stream = None
 
 
 def _stream(stream):
-    import torch
+    """The HIP stream handle of ``stream`` (an int, a torch stream, or None:
+    the current stream of the current device)."""
     if stream is None:
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        # the handle alone: building the torch.cuda.Stream object around it
+        # takes 2.7 us, more than a call's argument checks (0.9 us) and as
+        # long as a kernel launch
+        global _raw_stream
+        if _raw_stream is None:
+            import torch
+            if not torch.cuda.is_initialized():
+                return torch.cuda.current_stream().cuda_stream
+            device, raw = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+            _raw_stream = lambda: raw(device())
+        return _raw_stream()
     if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
+        return stream
+    return stream.cuda_stream
 
 
-def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr())
+def _ptr(t) -> int:
+    return t.data_ptr()
 
 
 def _nbytes(t) -> int:
@@ -254,15 +273,16 @@ def im2win_conv2d(x, w, stride: int, ws=None, out=None, stream=None):
     """Transform + conv on the current stream; allocates what is not given.
 
     Returns (out, ws)."""
-    import torch
     N, H_i, W_i, C_i = x.shape
     K_h, K_w, _, C_o = w.shape
-    H_o, W_o = conv_output_dims(H_i, W_i, K_h, K_w, stride)
-    need = conv_workspace_bytes(N, C_i, H_i, W_i, C_o, K_h, K_w, stride, x.dtype)
-    if ws is None:
-        ws = torch.empty(need, dtype=torch.uint8, device=x.device)
-    if out is None:
-        out = torch.empty((N, H_o, W_o, C_o), dtype=x.dtype, device=x.device)
+    if ws is None or out is None:  # given buffers are checked by the calls themselves
+        import torch
+        H_o, W_o = conv_output_dims(H_i, W_i, K_h, K_w, stride)
+        need = conv_workspace_bytes(N, C_i, H_i, W_i, C_o, K_h, K_w, stride, x.dtype)
+        if ws is None:
+            ws = torch.empty(need, dtype=torch.uint8, device=x.device)
+        if out is None:
+            out = torch.empty((N, H_o, W_o, C_o), dtype=x.dtype, device=x.device)
     conv_im2win_transform(x, ws, C_o, K_h, K_w, stride, stream)
     conv_for_dtype(x.dtype)(ws, w, out, N, C_i, H_i, W_i, stride, stream)
     return out, ws
@@ -290,7 +310,7 @@ def conv_im2win_chunked(x, w, out, ws, stride: int, n_chunk: int, stream=None, a
     K_h, K_w, C_i2, C_o = w.shape
     if C_i2 != C_i:
         raise ValueError("filter has %d input channels, layer has %d" % (C_i2, C_i))
-    aux = ctypes.c_void_p(None) if aux_stream is None else _stream(aux_stream)
+    aux = None if aux_stream is None else _stream(aux_stream)
     rc = load_library().conv_im2win_chunked(
         _ptr(x), _ptr(w), _ptr(out), _ptr(ws), _nbytes(ws), N, C_i, H_i, W_i, C_o, K_h, K_w,
         stride, n_chunk, _dtype_code(x.dtype), _stream(stream), aux)
