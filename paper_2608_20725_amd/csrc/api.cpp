@@ -267,7 +267,7 @@ int conv32(void *ws, int64_t ws_bytes, const float *filt_khkwcico, float *out_nh
         return launch_status(launch_conv_fp32_mfma(sh, plan, tu, filt_khkwcico, packed, out_nhwc, ws, st));
     if ((rc = launch_status(launch_pack_fp32(sh, plan, filt_khkwcico, packed, st))) != IM2WIN_OK)
         return rc;
-    return launch_status(launch_conv_fp32(sh, plan, tu, ws, packed, out_nhwc, st));
+    return launch_status(launch_conv_fp32(sh, plan, tu, ws, filt_khkwcico, packed, out_nhwc, st));
 }
 
 }  // namespace

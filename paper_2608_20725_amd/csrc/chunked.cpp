@@ -98,7 +98,8 @@ int enqueue_chunks(const void *in, const void *filt, void *out, char *wsb, const
         if ((rc = launch_status(launch_transform(sh, inc, wsl, cs, tu))) != IM2WIN_OK)
             return rc;
         if (dt == IM2WIN_F32)
-            rc = launch_status(launch_conv_fp32(sh, p32, tu, wsl, packed, reinterpret_cast<float *>(outc), cs));
+            rc = launch_status(launch_conv_fp32(sh, p32, tu, wsl, static_cast<const float *>(filt), packed,
+                                                reinterpret_cast<float *>(outc), cs));
         else
             rc = launch_status(launch_conv_fp16(sh, p16, tu, wsl, static_cast<const uint16_t *>(filt), packed,
                                                 reinterpret_cast<uint16_t *>(outc), cs,

@@ -372,7 +372,7 @@ hipError_t launch_transform(const Shape &sh, const void *in, void *ws, hipStream
 hipError_t launch_pack_fp32(const Shape &sh, const Plan32 &p, const float *filt, void *packed, hipStream_t st);
 // Dma and Regs plans (Mfma plans pack and launch through launch_conv_fp32_mfma).
 hipError_t launch_conv_fp32(const Shape &sh, const Plan32 &p, const Tuning &t, const void *ws,
-                            const void *packed, float *out, hipStream_t st);
+                            const float *filt, const void *packed, float *out, hipStream_t st);
 // fp32 on the matrix cores: whether the layer can run there (C_i a multiple
 // of 4, offsets in range), the bytes of its packed filter, and the launch
 // (filter pack, then conv).
@@ -403,8 +403,10 @@ hipError_t launch_conv_fp32_cols(const Shape &sh, int v, const Tuning &t, const 
 int stem32_plan(const Shape &sh);
 int stem32_default(const Shape &sh);
 const char *stem32_name(int v);
-hipError_t launch_conv_fp32_stem(const Shape &sh, int v, const void *ws, const void *packed, float *out,
-                                 hipStream_t st);
+// (the small-grid variants read the caller's filter: nothing is packed for them)
+bool stem32_small(int v);
+hipError_t launch_conv_fp32_stem(const Shape &sh, int v, const void *ws, const float *filt, const void *packed,
+                                 float *out, hipStream_t st);
 // Register-staged fp32 kernel: whether a tile can run the layer, its name.
 bool regs32_fits(const Shape &sh, int v);
 const char *regs32_name(int v);

@@ -505,6 +505,8 @@ bool regs32_fits(const Shape &sh, int v)
 
 hipError_t launch_pack_fp32(const Shape &sh, const Plan32 &p, const float *filt, void *packed, hipStream_t st)
 {
+    if (p.fam == Fam32::Stem && stem32_small(p.v))
+        return hipSuccess;  // reads the caller's filter
     Pack32Args a;
     a.filt = filt;
     a.packed = static_cast<float *>(packed);
@@ -527,12 +529,12 @@ hipError_t launch_pack_fp32(const Shape &sh, const Plan32 &p, const float *filt,
 }
 
 hipError_t launch_conv_fp32(const Shape &sh, const Plan32 &p, const Tuning &t, const void *ws,
-                            const void *packed, float *out, hipStream_t st)
+                            const float *filt, const void *packed, float *out, hipStream_t st)
 {
     if (p.fam == Fam32::Dma)
         return launch_conv_fp32_dma(sh, p.v, t, ws, packed, out, st);
     if (p.fam == Fam32::Stem)
-        return launch_conv_fp32_stem(sh, p.v, ws, packed, out, st);
+        return launch_conv_fp32_stem(sh, p.v, ws, filt, packed, out, st);
     if (p.fam == Fam32::Cols)
         return launch_conv_fp32_cols(sh, p.v, t, ws, packed, out, st);
     C32Args a;

@@ -125,6 +125,71 @@ __global__ __launch_bounds__(64 * kS32Waves) void conv_fp32_stem(S32Args a)
     }
 }
 
+// The same sums for small grids: one wave per 64 pixels and 8 channels
+// instead of one per 64 pixels and all of them, so that one small image is
+// not four workgroups that each walk every channel, and the caller's filter
+// read as it is (lane t holds the 8 values of tap t, broadcast to the FMAs
+// with a lane read), which saves the pack launch.  Same taps in the same
+// order as above, bit for bit.
+struct S32SmallArgs {
+    const float *ws, *filt;
+    float *out;
+    uint32_t P, K, Co, Wo, Ci, Kh, Kw, ncg;
+    uint64_t L, S;
+    FastDiv div_Wo, div_khci, div_ci;
+};
+
+constexpr int kSmallChannels = 8;
+
+template <int KMAX>
+__global__ __launch_bounds__(64) void conv_fp32_stem_small(S32SmallArgs a)
+{
+    constexpr int KW4 = (KMAX + 3) / 4, CPW = kSmallChannels;
+    const uint32_t lane = threadIdx.x;
+    const uint32_t blk = blockIdx.x / a.ncg, c0 = (blockIdx.x - blk * a.ncg) * CPW;
+    const uint32_t p = blk * 64 + lane;
+    const bool live = p < a.P;
+    const uint32_t q = live ? fdiv(p, a.div_Wo) : 0u;
+    const uint64_t w0 = live ? (uint64_t)q * a.L + (uint64_t)(p - q * a.Wo) * a.S : 0u;
+    const char *win = reinterpret_cast<const char *>(a.ws + w0);
+    u32x4 xr[KW4];  // values past K: at most 60 bytes past the last window, inside the pad
+#pragma unroll
+    for (int g = 0; g < KW4; ++g)
+        __builtin_memcpy(&xr[g], win + 16 * g, 16);
+    // tap `lane` of window order is filter row (u*K_w + v)*C_i + r
+    float f[CPW];
+    const uint32_t k = lane < a.K ? lane : a.K - 1;
+    const uint32_t v = fdiv(k, a.div_khci), rem = k - v * (a.Kh * a.Ci);
+    const uint32_t u = fdiv(rem, a.div_ci), r = rem - u * a.Ci;
+    const float *fr = a.filt + ((u * a.Kw + v) * a.Ci + r) * a.Co + c0;
+#pragma unroll
+    for (int j = 0; j < CPW; j += 4) {
+        const float4 t = c0 + j < a.Co ? *reinterpret_cast<const float4 *>(fr + j) : make_float4(0.f, 0.f, 0.f, 0.f);
+        f[j] = t.x; f[j + 1] = t.y; f[j + 2] = t.z; f[j + 3] = t.w;
+    }
+    float acc[CPW];
+#pragma unroll
+    for (int j = 0; j < CPW; ++j)
+        acc[j] = 0.f;
+#pragma unroll
+    for (int t = 0; t < KMAX; ++t) {
+        if (t < (int)a.K) {
+            const float x = __uint_as_float(xr[t / 4][t % 4]);
+#pragma unroll
+            for (int j = 0; j < CPW; ++j)
+                acc[j] = __builtin_fmaf(
+                    x, __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(f[j]), t)), acc[j]);
+        }
+    }
+    if (!live)
+        return;
+#pragma unroll
+    for (int j = 0; j < CPW; j += 4)
+        if (c0 + j < a.Co)
+            *reinterpret_cast<float4 *>(a.out + (uint64_t)p * a.Co + c0 + j) =
+                make_float4(acc[j], acc[j + 1], acc[j + 2], acc[j + 3]);
+}
+
 }  // namespace
 
 // Windows not 16-byte aligned (C_i % 4 != 0), undilated, K <= 32, C_o a
@@ -146,14 +211,52 @@ int stem32_plan(const Shape &sh)
 // half the vector peak; its gain is in loads and stores.
 int stem32_default(const Shape &sh)
 {
-    return sh.K <= 27 ? stem32_plan(sh) : -1;
+    const int v = sh.K <= 27 ? stem32_plan(sh) : -1;
+    // Small grids: up to 8192 waves of 64 pixels x 8 channels (eight per
+    // SIMD).  Conv call with its pack, us, full-channel waves against these:
+    // 3x3 C_i=3, 32x32 C_o=16, one image 11.1 / 4.5, 128 images (3600 waves)
+    // 12.3 / 9.4; one 224x224 image C_o=64 (6168) 18.4 / 11.9; even at 11224
+    // (stride 2 at 129x124, 23 images: 19.8 / 19.4), behind at 24648 (four
+    // 224x224 images: 24.1 / 30.4).  Four channels per wave measured up to
+    // 20 % behind eight.
+    if (v >= 0 && (sh.P + 63) / 64 * ((sh.Co + kSmallChannels - 1) / kSmallChannels) <= 8192)
+        return v + 3;
+    return v;
 }
 
-const char *stem32_name(int v) { return v == 0 ? "k16" : v == 1 ? "k27" : "k32"; }
-
-hipError_t launch_conv_fp32_stem(const Shape &sh, int v, const void *ws, const void *packed, float *out,
-                                 hipStream_t st)
+// Variants 0..2 and their small-grid forms 3..5.
+const char *stem32_name(int v)
 {
+    static const char *names[] = {"k16", "k27", "k32", "k16c8", "k27c8", "k32c8"};
+    return names[v];
+}
+
+bool stem32_small(int v) { return v >= 3; }
+
+hipError_t launch_conv_fp32_stem(const Shape &sh, int v, const void *ws, const float *filt, const void *packed,
+                                 float *out, hipStream_t st)
+{
+    if (stem32_small(v)) {
+        S32SmallArgs a;
+        a.ws = static_cast<const float *>(ws);
+        a.filt = filt;
+        a.out = out;
+        a.P = (uint32_t)sh.P; a.K = (uint32_t)sh.K; a.Co = (uint32_t)sh.Co; a.Wo = (uint32_t)sh.Wo;
+        a.Ci = (uint32_t)sh.Ci; a.Kh = (uint32_t)sh.Kh; a.Kw = (uint32_t)sh.Kw;
+        a.L = (uint64_t)sh.L; a.S = (uint64_t)sh.S;
+        a.div_Wo = make_fastdiv(a.Wo);
+        a.div_khci = make_fastdiv(a.Kh * a.Ci);
+        a.div_ci = make_fastdiv(a.Ci);
+        a.ncg = (uint32_t)((sh.Co + kSmallChannels - 1) / kSmallChannels);
+        const int64_t wgs = (sh.P + 63) / 64 * a.ncg;
+        if (wgs > 0x7fffffff)
+            return hipErrorInvalidValue;
+        static const void *const fs[] = {(const void *)&conv_fp32_stem_small<16>,
+                                         (const void *)&conv_fp32_stem_small<27>,
+                                         (const void *)&conv_fp32_stem_small<32>};
+        void *args[] = {&a};
+        return hipLaunchKernel(fs[v - 3], dim3((uint32_t)wgs), dim3(64), args, 0, st);
+    }
     S32Args a;
     a.ws = static_cast<const float *>(ws);
     a.packed = static_cast<const float *>(packed);

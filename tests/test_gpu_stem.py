@@ -12,6 +12,7 @@ import torch
 
 import oracle
 from gpu_util import Run, TOL, assert_kernel, check_full, oracle_inputs, rel_err, say
+import paper_2608_20725_amd as pkg
 from paper_2608_20725_amd import workloads
 
 pytestmark = pytest.mark.gpu
@@ -149,3 +150,23 @@ def test_stem32_nonfinite_and_integer(monkeypatch):
     with np.errstate(invalid="ignore", over="ignore"):
         ref = oracle.conv(x.double().numpy(), w.double().numpy(), s)
     assert np.array_equal(np.isfinite(run.out.cpu().numpy()), np.isfinite(ref))
+
+
+@pytest.mark.parametrize("shape", [
+    (1, 3, 32, 32, 16, 3, 3, 1), (1, 1, 1, 1, 4, 1, 1, 1), (2, 3, 9, 8, 20, 3, 3, 2), (1, 5, 6, 30, 12, 2, 2, 1),
+    (3, 2, 7, 7, 36, 2, 4, 1), (1, 3, 66, 3, 8, 3, 3, 1), (5, 1, 13, 13, 28, 5, 5, 2),
+], ids=lambda s: "x".join(map(str, s)))
+def test_stem32_small_grid_same_bits(shape, monkeypatch):
+    """Small grids run one wave per 64 pixels and 8 channels, from the
+    caller's filter: the same FMA chains as the full-channel kernel, bit for
+    bit (channel counts off 8, pixel counts off 64, windows of 1 to 25 taps)."""
+    N, Ci, H, W, Co, Kh, Kw, s = shape
+    assert pkg.conv_im2win_kernel_name(*shape, torch.float32).endswith("c8")
+    x, w = workloads.draw(N, Ci, H, W, Co, Kh, Kw, 11)
+    small = Run(x, w, s, torch.float32)
+    check_full(small, x, w)
+    small.check_workspace_guard()
+    small.check_out_guards()
+    monkeypatch.setenv("IM2WIN_FP32_KERNEL", "stem")
+    full = Run(x, w, s, torch.float32)
+    assert torch.equal(small.out.view(torch.int32), full.out.view(torch.int32))
