@@ -119,11 +119,7 @@ int64_t workspace_bytes(const Shape &sh, int dt)
     const int64_t base = sh.pad_end + packed_filter_bytes(sh, dt);
     if (dt == IM2WIN_F32)
         return base;
-    // the split-K region of the plan a call makes without tuning variables
-    Plan16 p;
-    if (plan_fp16(sh, default_tuning(), &p) != IM2WIN_OK)
-        return base;
-    return base + split_bytes(sh, p);
+    return base + split_reserve_bytes(sh);
 }
 
 bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }

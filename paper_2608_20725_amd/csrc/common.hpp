@@ -457,11 +457,14 @@ hipError_t launch_conv_fp16_direct(const Shape &sh, int v, const Tuning &t, cons
                                    uint16_t *out, hipStream_t st, Op16 op);
 hipError_t launch_conv_fp16_col(const Shape &sh, int v, const Tuning &t, const void *ws, const void *packed,
                                 uint16_t *out, hipStream_t st, Op16 op);
-// Row-per-pixel fp16 tiles: default for the layer, name, and the K split the
-// planner picks for a tile (1: none).
+// Row-per-pixel fp16 tiles: default for the layer and name; 128 x 128 tiles
+// of the layer; whether bm-row channel tiles suit its C_o; the workspace
+// bytes kept for fp32 partial tiles.
 int pipe_default(const Shape &sh);
 const char *pipe_name(int v);
-int pipe_split_default(const Shape &sh, int v);
+int64_t tiles128(const Shape &sh);
+bool rows_fit(const Shape &sh, int64_t bm);
+int64_t split_reserve_bytes(const Shape &sh);
 // Output tiles of a row-per-pixel variant on a layer, and its 64-tap stages.
 int64_t pipe_tiles(const Shape &sh, int v);
 int64_t pipe_tile_elems(int v);

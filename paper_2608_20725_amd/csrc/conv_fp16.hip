@@ -797,6 +797,12 @@ const PipeVariant *pipe_variants(int *n)
         pipe_variant<2, 2, 2, 4, 2>("c128p256s2w8"),
         // one ring slot: no double buffering (ablation)
         pipe_variant<2, 2, 2, 2, 1>("c128p128s1"),
+        // deeper rings for grids of at most one workgroup per CU, where no
+        // second workgroup covers a stage's load latency
+        pipe_variant<1, 1, 2, 2, 4>("c64p64s4"),
+        pipe_variant<2, 1, 2, 2, 4>("c128p64s4"),
+        pipe_variant<2, 1, 2, 4, 3>("c128p128s3w8"),
+        pipe_variant<2, 2, 4, 2, 3>("c256p128s3w8"),
     };
     *n = (int)(sizeof v / sizeof v[0]);
     return v;
@@ -847,61 +853,95 @@ int64_t pipe_tile_elems(int v)
     return (int64_t)pv.bm * pv.bn;
 }
 
-namespace {
-
-// K split of the 128 x 128 two-slot tile on a layer with at most 128 such
-// tiles (fewer than one per CU) and at least 32 stages: the largest ks <= 4
-// whose partial tiles keep the whole workspace within the size of the
-// layer's im2col matrix; 1 when none does.  Measured on 3x3 C = 512 at 7x7
-// (128 images, 100 tiles, 72 stages): unsplit 64 x 128 tiles 331 TFLOP/s,
-// 128 x 128 tiles split 2 / 3 / 4 ways 350 / 376 / 408 (split 3 and 4 need
-// more workspace than im2col); with more tiles or fewer stages the split's
-// second kernel and partial-tile traffic cost more than it gains.
-int split128(const Shape &sh)
+// Bytes conv_workspace_bytes reserves after the packed filter for fp32
+// partial tiles: ks 128 x 128 tiles per output tile of a layer with at most
+// 128 of them and at least 32 stages, for the largest ks <= 4 that keeps the
+// workspace within the layer's im2col matrix.  Plans no longer split K by
+// default (the deeper rings below fill such grids without partial sums: 3x3
+// C=512 at 14x14, 16 images, split two ways 39.9 us, c128p64s4 29.2), but
+// the size is part of the interface, and a forced split uses the room.
+int64_t split_reserve_bytes(const Shape &sh)
 {
     const int v = pipe_find("c128p128s2");
     const int64_t tiles = pipe_tiles(sh, v), nst = sh.K_pad / BK;
     if (sh.Ci % 8 != 0 || sh.Co < 128 || tiles > 128 || nst < 32)
-        return 1;
+        return 0;
+    // layers that ran a column-staged kernel have no such region
+    if (sh.Kw == 3 && sh.Co <= 256 && col_fits(sh, col_find(sh.Co == 128 ? "k3c128p128t32s2" : "k3c64p128t32s2")))
+        return 0;
+    if (sh.Kw == 7 && sh.Co == 128 && col_fits(sh, col_find("k7c64p256t16s3")))
+        return 0;
     const int64_t base = sh.pad_end + sh.Co_pad * sh.Kw * sh.Tp * 2;  // window tensor, pad, packed filter
     const int64_t im2col = sh.P * sh.K * 2;
     for (int ks = 4; ks >= 2; --ks) {
-        const int64_t spl = (nst + ks - 1) / ks;
-        if ((ks - 1) * spl < nst && base + ks * tiles * pipe_tile_elems(v) * 4 <= im2col)
-            return ks;
+        const int64_t spl = (nst + ks - 1) / ks, bytes = ks * tiles * pipe_tile_elems(v) * 4;
+        if ((ks - 1) * spl < nst && base + bytes <= im2col)
+            return bytes;
     }
-    return 1;
+    return 0;
 }
 
-}  // namespace
+// Whether channel tiles of bm rows pad C_o by at most a fifth or so (the
+// padded rows are loaded and multiplied like the others).
+bool rows_fit(const Shape &sh, int64_t bm)
+{
+    return round_up(sh.Co, bm) * 10 <= sh.Co * 13;
+}
+
+int64_t tiles128(const Shape &sh)
+{
+    return ((sh.P + 127) / 128) * ((sh.Co + 127) / 128);
+}
 
 int pipe_default(const Shape &sh)
 {
-    // Defaults, measured per layer on MI355X: shapes that leave LDS for
-    // two workgroups per CU (32x128, 64x128, 128x128); 64x128 also when a
-    // 128x128 grid would give fewer workgroups than CUs (S11: 280 vs 220
-    // TFLOP/s); 256x256 over eight waves when its grid fills 128 to 256
-    // CUs (cfg4 616 vs 575, S4 670 vs 646; with fewer tiles it starves
-    // the chip, with more the second round runs partly empty).
+    // Measured per layer on MI355X (conv call with its pack, us).  What binds
+    // these tiles is the L2 -> LDS traffic (about 13 TB/s over the chip, 30
+    // bytes per clock and CU), so tiles are as large as the grid allows.
     auto tiles = [&](int64_t bm, int64_t bn) { return ((sh.P + bn - 1) / bn) * ((sh.Co + bm - 1) / bm); };
+    const int64_t t128 = tiles128(sh), t256 = tiles(256, 128);
+    // C_o that fills 64-channel rows much better than 128-channel ones (144:
+    // 192 against 256; 7x7 64 -> 144 dilated 47.4 vs 34.5)
+    const bool half = round_up(sh.Co, 128) * 4 > round_up(sh.Co, 64) * 5;
+    // 256 x 128 over eight waves, three slots, one workgroup per CU: half
+    // again fewer bytes per FLOP than 128 x 128, so long windows run faster
+    // where the grid comes out at whole rounds of the CUs
+    const bool wide = sh.Co >= 256 && sh.K >= 1024 && rows_fit(sh, 256);
     if (sh.Co <= 32)
         return pipe_find("c32p128s3");
-    if (fp16_single_slot_rows(sh))
+    if (fp16_single_slot_rows(sh)) {
+        // 3x3 stride 2 C=256 at 56x56, 128 images (729 tiles, 2.85 rounds)
+        // 139 vs 130; 3x3 C=256 at 28x28 (784 tiles, 3.06 rounds) 134 vs 152
+        if (wide && t256 * 10 >= (t256 + 255) / 256 * 256 * 9)
+            return pipe_find("c256p128s3w8");
         return pipe_find("c128p128s1");
-    // too few 128 x 128 tiles to fill the chip: split K over them where the
-    // workspace allows, else 64 x 128 tiles
-    if (split128(sh) > 1)
-        return pipe_find("c128p128s2");
-    if (sh.Co <= 64 || tiles(128, 128) < 256)
+    }
+    if (sh.Co <= 64 || half)
         return pipe_find("c64p128s3");
+    // At most one workgroup per CU: a deeper ring instead of a second
+    // workgroup covers the loads, in the largest tile that spreads over the
+    // CUs.  Against two-slot 128 x 128 / three-slot 64 x 128 tiles: c64p64s4
+    // 3x3 C=512 at 7x7, 24 images, 24.1 vs 31.2; c128p64s4 same layer, 128
+    // images, 30.4 vs 32.0; c128p128s3w8 3x3 C=512 at 14x14, 32 images, 38.0
+    // vs 46.3, 5x5 96 -> 256 at 24x24, 32 images, 26.0 vs 32.0, 1x1 512 ->
+    // 2048 at 7x7, 32 images, 14.0 vs 15.2.
+    if (t128 <= 64)
+        return pipe_find("c64p64s4");
+    if (t128 <= 128)
+        return pipe_find("c128p64s4");
+    if (t128 <= 256)
+        return pipe_find("c128p128s3w8");
+    // up to two 128 x 128 tiles per CU, unevenly spread: one 256 x 128 tile
+    // each instead (3x3 C=256 dilated at 28x28, 32 images, 392 / 196 tiles,
+    // 42.6 vs 40.2; 3x3 C=512 at 14x14, 64 images, 67.4 vs 56.9)
+    if (t128 <= 512 && wide)
+        return pipe_find("c256p128s3w8");
+    // 256 x 256 over eight waves when its grid fills 128 to 256 CUs (cfg4
+    // 616 vs 575 TFLOP/s, S4 670 vs 646; with fewer tiles it starves the
+    // chip, with more the second round runs partly empty)
     if (tiles(256, 256) >= 128 && tiles(256, 256) <= 256 && sh.Co >= 256)
         return pipe_find("c256p256s2w8");
     return pipe_find("c128p128s2");
-}
-
-int pipe_split_default(const Shape &sh, int v)
-{
-    return v == pipe_find("c128p128s2") ? split128(sh) : 1;
 }
 
 hipError_t launch_pack_fp16(const Shape &sh, const Plan16 &p, const uint16_t *filt, void *packed, hipStream_t st,

@@ -586,10 +586,15 @@ int col_default(const Shape &sh)
     // lose (S5: 536 vs 636), so those layers keep the row kernel.
     auto tiles = [&](int64_t bn) { return ((sh.P + bn - 1) / bn) * ((sh.Co + 255) / 256); };
     const char *name = nullptr;
+    // grids of at most one 128 x 128 tile per CU run the row kernel's deeper
+    // rings (3x3 C=128 at 28x28, 32 images: 17.0 vs 15.9 us; 3x3 C=256 at
+    // 14x14, 64 images: 26.4 vs 24.8), short 3x3 windows (K <= 576) excepted
+    const bool small = sh.Co > 64 && tiles128(sh) <= 256 && !(sh.Kw == 3 && sh.Co <= 128 && sh.K <= 576);
     // the one-slot row kernel is faster on many-tile layers with C_o >= 128,
     // except 3x3 layers with C_o <= 128 (3x3 64 -> 128 at 112x112: column
-    // kernel 664 vs 636 TFLOP/s)
-    if (fp16_single_slot_rows(sh) && !(sh.Kw == 3 && sh.Co <= 128))
+    // kernel 664 vs 636 TFLOP/s) or stride 1 (3x3 C=256 at 28x28: 124 vs 134
+    // us; with stride 2 at 56x56 past 150 vs 139)
+    if (fp16_single_slot_rows(sh) && !(sh.Kw == 3 && (sh.Co <= 128 || sh.s == 1)))
         return -1;
     // C_o <= 64: 64 x 128 tiles, three workgroups per CU, more bytes in
     // flight for these HBM-bound layers (3x3 C=64 at 56x56: 484 vs 431
@@ -599,7 +604,7 @@ int col_default(const Shape &sh)
     // 64 < C_o <= 128: one 128 x 128 tile reads each window once where two
     // 64-channel tiles read it twice (3x3 64 -> 128 at 112x112: 771 vs 714
     // TFLOP/s; 128 -> 128 at 28x28: 646 vs 603-639)
-    else if (sh.Kw == 3 && sh.Co <= 128)
+    else if (sh.Kw == 3 && sh.Co <= 128 && !small)
         name = "k3c128p128t32s2";
     // 7x7: with stride 1 and C_o <= 64 the 64 x 128 tile (two-slot ring,
     // 49 KiB, three workgroups per CU) measured 785 vs 713 TFLOP/s
@@ -613,13 +618,19 @@ int col_default(const Shape &sh)
         name = "k7c64p256t32s2";
     else if (sh.Kw == 7 && sh.Co <= 128)
         name = "k7c64p256t16s3";
-    else if (sh.Kw == 3 && tiles(192) >= 160 && tiles(192) <= 256)
+    // eight-wave 256-channel tiles where they pad few channels (C_o = 320:
+    // 35.8 vs 27.7 us with 128-channel tiles)
+    else if (sh.Kw == 3 && sh.Co > 128 && rows_fit(sh, 256) && tiles(192) >= 160 && tiles(192) <= 256)
         name = "k3c256p192t32s2w8";
-    else if (sh.Kw == 3 && tiles(256) >= 160 && tiles(256) <= 256)
+    else if (sh.Kw == 3 && sh.Co > 128 && rows_fit(sh, 256) && tiles(256) >= 160 && tiles(256) <= 256)
         name = "k3c256p256t32s2w8";
-    // 3x3 C=256 at 14x14 (128 images): four 64 x 128 channel tiles per
-    // pixel tile beat the 128 x 128 row kernel, 583 vs 529 TFLOP/s
-    else if (sh.Kw == 3 && sh.Co <= 256)
+    // stride 1, more than one 128 x 128 tile per CU: each window column
+    // loaded once for three filter columns leaves less L2 traffic than the
+    // row kernel (3x3 C=256 at 14x14, 128 images: 34.5 vs 36.4 us, 35.9 with
+    // 64 x 128 tiles; 256 -> 512 at 12x12: 39.8 vs 43.5)
+    else if (sh.Kw == 3 && sh.Co > 128 && sh.s == 1 && !small && rows_fit(sh, 128))
+        name = "k3c128p128t32s2";
+    else if (sh.Kw == 3 && sh.Co > 128 && sh.Co <= 256 && !small)
         name = "k3c64p128t32s2";
     else
         return -1;

@@ -381,6 +381,12 @@ int direct_default(const Shape &sh)
     }
     if (best < 0)
         return -1;
+    // With long windows the row kernel's 64 x 64 tile with four slots is
+    // ahead where this one would use as large a tile (3x3 C=512 at 7x7, 24
+    // images: 24.1 vs 29.3 us; 3x3 C=256 at 14x14, 12 images: 14.8 vs 16.4;
+    // 1x1 1024 -> 256 at 14x14, 16 images: 10.3 vs 9.8).
+    if (aligned && sh.K >= 1536 && v[best].bm == 64 && v[best].bn == 64)
+        return -1;
     // the largest tile the layer's channels allow decides whether the grid is small
     const int64_t big = sh.Co % 4 == 0 ? 64 : 32;
     const int64_t tiles = ((sh.P + big - 1) / big) * ((sh.Co + big - 1) / big);
