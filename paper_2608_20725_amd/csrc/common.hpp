@@ -438,7 +438,9 @@ bool fp16_single_slot_rows(const Shape &sh);
 int seg_default(const Shape &sh);
 bool seg_fits(const Shape &sh, int v);
 const char *seg_name(int v);
-hipError_t launch_conv_fp16_seg(const Shape &sh, int v, const void *ws, const void *packed,
+// (variants that read the caller's filter: nothing is packed for them)
+bool seg_reads_filter(int v);
+hipError_t launch_conv_fp16_seg(const Shape &sh, int v, const void *ws, const uint16_t *filt, const void *packed,
                                 uint16_t *out, hipStream_t st, Op16 op);
 // Short-window fp16 kernel (windows not 16-byte aligned, K <= 160, C_o <= 128,
 // C_o % 8 == 0): its variant for the layer (-1: cannot run it), name, launch.

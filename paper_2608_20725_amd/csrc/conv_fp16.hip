@@ -948,7 +948,7 @@ hipError_t launch_pack_fp16(const Shape &sh, const Plan16 &p, const uint16_t *fi
                             void *split)
 {
     (void)split;
-    if (p.fam == Fam16::Direct)
+    if (p.fam == Fam16::Direct || (p.fam == Fam16::Seg && seg_reads_filter(p.v)))
         return hipSuccess;  // reads the caller's filter
     PackArgs a;
     a.filt = filt;
@@ -994,7 +994,7 @@ hipError_t launch_conv_fp16(const Shape &sh, const Plan16 &p, const Tuning &t, c
     if (p.fam == Fam16::Col)
         return launch_conv_fp16_col(sh, p.v, t, ws, packed, out, st, op);
     if (p.fam == Fam16::Seg)
-        return launch_conv_fp16_seg(sh, p.v, ws, packed, out, st, op);
+        return launch_conv_fp16_seg(sh, p.v, ws, filt, packed, out, st, op);
     if (p.fam == Fam16::Stem)
         return launch_conv_fp16_stem(sh, p.v, ws, packed, out, st, op);
     C16Args a;

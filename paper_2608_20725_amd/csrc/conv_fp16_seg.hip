@@ -345,8 +345,318 @@ int64_t seg_granules_needed(const Shape &sh, int bn, int64_t runs_max)
     return worst;
 }
 
+// ---------------------------------------------------------------------------
+// The same strips, one wave at a time, with the filter kept in LDS.
+//
+// What bound the tiles above on the large stems is not the matrix cores (17 %
+// busy on 11x11 stride 4) but their phases: every 128-pixel tile waits for its
+// segments, streams the whole filter from L2 (74 KB beside 34 KB of windows)
+// between barriers, and stores.  Here a persistent workgroup keeps the filter
+// of its channels in LDS for good (transposed once from the caller's filter,
+// so nothing is packed), and each of its eight waves works alone on blocks of
+// 32 consecutive pixels of one strip: its segment is one span, loaded
+// unaligned into registers a block ahead and written to the wave's LDS area,
+// so that the span's first element is 16-byte aligned there.  Pixel n then
+// starts 2*n*S bytes in, and its operand is read in AL-byte pieces, AL = 8, 4
+// or 2 the largest that divides 2*S.  No barrier after the filter is loaded.
+struct SegWArgs {
+    const uint16_t *ws, *filt;
+    uint16_t *out;
+    uint32_t K, Co, Wo, Ci, Kh, Kw, S;
+    uint64_t L;
+    uint32_t nblk, wps;      // 32-pixel blocks in all and per strip
+    uint32_t nks, pitch;     // 16-tap steps; bytes of a filter row in LDS (an odd number of 16-byte chunks)
+    uint32_t segb;           // bytes of a wave's area
+    FastDiv div_wps, div_khci, div_ci;
+};
+
+constexpr int kSegWWaves = 8;
+
+// NG: 16-byte granules of a segment per lane; WPE: waves per SIMD the
+// registers are held to.
+template <class E, int WM, int NG, int AL, int WPE>
+__global__ __launch_bounds__(64 * kSegWWaves, WPE) void conv_fp16_segw(SegWArgs a)
+{
+    typedef typename E::v8 v8;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const uint32_t tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t ch0 = blockIdx.y * (32 * WM);
+    char *const area = smem + 32 * WM * a.pitch + wave * a.segb;
+
+    uint32_t blk = blockIdx.x * kSegWWaves + wave;
+    const uint32_t step = gridDim.x * kSegWWaves;
+    u32x4 pre[NG];
+    // granules of block b's span, from its first element (2-byte aligned) to
+    // its last pixel's last step: at most 45 bytes past the last window
+    auto load = [&](uint32_t b) {
+        const uint32_t q = fdiv(b, a.div_wps), n0 = (b - q * a.wps) * 32;
+        const uint32_t npx = a.Wo - n0 < 32 ? a.Wo - n0 : 32;
+        const char *src = reinterpret_cast<const char *>(a.ws + (uint64_t)q * a.L + (uint64_t)n0 * a.S);
+        const uint32_t need = ((npx - 1) * a.S + 16 * a.nks) * 2;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const uint32_t off = (g * 64 + lane) * 16;
+            if (off < need)
+                __builtin_memcpy(&pre[g], src + off, 16);
+        }
+    };
+    if (blk < a.nblk)
+        load(blk);
+
+    // filter: row j, tap k at smem + j*pitch + 2*k; a thread moves 8 taps of a
+    // channel pair.  Zero past K and past C_o.
+    const uint32_t units = 16 * WM * a.nks * 2;
+    for (uint32_t t = tid; t < units; t += 64 * kSegWWaves) {
+        const uint32_t k8 = t / (16 * WM), cp = t - k8 * (16 * WM);
+        const uint32_t ch = ch0 + 2 * cp;
+        uint32_t k = 8 * k8, x[8];
+        uint32_t v = fdiv(k, a.div_khci), rem = k - v * (a.Kh * a.Ci);
+        uint32_t u = fdiv(rem, a.div_ci), r = rem - u * a.Ci;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            x[e] = 0u;
+            if (k < a.K && ch < a.Co) {
+                const uint16_t *src = a.filt + ((uint64_t)(u * a.Kw + v) * a.Ci + r) * a.Co + ch;
+                if (ch + 1 < a.Co)
+                    __builtin_memcpy(&x[e], src, 4);
+                else
+                    x[e] = *src;
+            }
+            ++k;
+            if (++r == a.Ci) {
+                r = 0;
+                if (++u == a.Kh) {
+                    u = 0;
+                    ++v;
+                }
+            }
+        }
+        u32x4 lo, hi;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            lo[d] = __builtin_amdgcn_perm(x[2 * d + 1], x[2 * d], 0x05040100u);
+            hi[d] = __builtin_amdgcn_perm(x[2 * d + 1], x[2 * d], 0x07060302u);
+        }
+        *reinterpret_cast<u32x4 *>(smem + (2 * cp) * a.pitch + 16 * k8) = lo;
+        *reinterpret_cast<u32x4 *>(smem + (2 * cp + 1) * a.pitch + 16 * k8) = hi;
+    }
+    __syncthreads();
+
+    const char *const arow = smem + (lane & 31) * a.pitch + 16 * (lane >> 5);
+    const char *const brow = area + (lane & 31) * a.S * 2 + 16 * (lane >> 5);
+    constexpr uint32_t SP = 64 * WM + 16;  // bytes of a staged output row
+    for (; blk < a.nblk; blk += step) {
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const uint32_t off = (g * 64 + lane) * 16;
+            if (off < a.segb)
+                *reinterpret_cast<u32x4 *>(area + off) = pre[g];
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the wave's span is in LDS
+        __builtin_amdgcn_wave_barrier();
+        if (blk + step < a.nblk)
+            load(blk + step);
+
+        floatx16 acc[WM];
+#pragma unroll
+        for (int i = 0; i < WM; ++i)
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                acc[i][e] = 0.f;
+        auto frags = [&](uint32_t ks, v8 (&af)[WM], u32x4 &b) {
+#pragma unroll
+            for (int i = 0; i < WM; ++i)
+                af[i] = *reinterpret_cast<const v8 *>(arow + 32 * i * a.pitch + 32 * ks);
+            const char *p = brow + 32 * ks;
+            if constexpr (AL == 8) {
+                const uint2 b0 = *reinterpret_cast<const uint2 *>(p), b1 = *reinterpret_cast<const uint2 *>(p + 8);
+                b = u32x4{b0.x, b0.y, b1.x, b1.y};
+            } else if constexpr (AL == 4) {
+                const uint32_t *w = reinterpret_cast<const uint32_t *>(p);
+                b = u32x4{w[0], w[1], w[2], w[3]};
+            } else {
+                // five aligned dwords, shifted by half a dword where the
+                // pixel starts on one
+                const uint32_t o = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char *)p;
+                const uint32_t *w = reinterpret_cast<const uint32_t *>(p - (o & 2u));
+                const uint32_t d[5] = {w[0], w[1], w[2], w[3], w[4]};
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    b[t] = __builtin_amdgcn_alignbyte(d[t + 1], d[t], o & 2u);
+            }
+        };
+        v8 af[2][WM];
+        u32x4 bf[2];
+        frags(0, af[0], bf[0]);
+        const uint32_t last = a.nks - 1;
+        uint32_t ks = 0;
+#pragma unroll 1
+        for (; ks + 2 <= last; ks += 2) {
+            frags(ks + 1, af[1], bf[1]);
+#pragma unroll
+            for (int i = 0; i < WM; ++i)
+                acc[i] = E::mfma(af[0][i], __builtin_bit_cast(v8, bf[0]), acc[i]);
+            frags(ks + 2, af[0], bf[0]);
+#pragma unroll
+            for (int i = 0; i < WM; ++i)
+                acc[i] = E::mfma(af[1][i], __builtin_bit_cast(v8, bf[1]), acc[i]);
+        }
+        if (ks < last) {
+#pragma unroll
+            for (int i = 0; i < WM; ++i)
+                acc[i] = E::mfma(af[0][i], __builtin_bit_cast(v8, bf[0]), acc[i]);
+            frags(last, af[0], bf[0]);
+        }
+        // the last step: taps past K belong to the next pixel and are cleared
+        const uint32_t k = 16 * last + 8 * (lane >> 5), nv = k < a.K ? a.K - k : 0u;
+#pragma unroll
+        for (uint32_t d = 0; d < 4; ++d)
+            bf[0][d] &= (2 * d < nv ? 0xffffu : 0u) | (2 * d + 1 < nv ? 0xffff0000u : 0u);
+#pragma unroll
+        for (int i = 0; i < WM; ++i)
+            acc[i] = E::mfma(af[0][i], __builtin_bit_cast(v8, bf[0]), acc[i]);
+
+        // round once, stage the block as [pixel][channel] in the wave's area,
+        // and store whole output rows
+        __builtin_amdgcn_wave_barrier();
+        const uint32_t q = fdiv(blk, a.div_wps), n0 = (blk - q * a.wps) * 32;
+        const uint32_t npx = a.Wo - n0 < 32 ? a.Wo - n0 : 32;
+#pragma unroll
+        for (int i = 0; i < WM; ++i)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                uint32_t h[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    h[e] = E::bits(acc[i][4 * g + e]);
+                *reinterpret_cast<uint2 *>(area + (lane & 31) * SP + (32 * i + 8 * g + 4 * (lane >> 5)) * 2) =
+                    make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+            }
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        __builtin_amdgcn_wave_barrier();
+        uint16_t *const o = a.out + ((uint64_t)q * a.Wo + n0) * a.Co + ch0;
+#pragma unroll
+        for (int t = 0; t < 2 * WM; ++t) {
+            const uint32_t c = t * 64 + lane, px = c / (4 * WM), cc = 8 * (c - px * (4 * WM));
+            const u32x4 v = *reinterpret_cast<const u32x4 *>(area + px * SP + 2 * cc);
+            if (px >= npx || ch0 + cc >= a.Co)
+                continue;
+            uint16_t *d = o + (uint64_t)px * a.Co + cc;
+            if (a.Co % 8 == 0) {
+                *reinterpret_cast<u32x4 *>(d) = v;
+            } else {
+#pragma unroll
+                for (uint32_t e = 0; e < 8; ++e)
+                    if (ch0 + cc + e < a.Co)
+                        d[e] = (uint16_t)(v[e / 2] >> (16 * (e % 2)));
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // the rows are read before the next span lands on them
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+struct SegWPlan {
+    const char *name;
+    int wm;
+};
+
+// Channels a workgroup keeps; the LDS the layer takes with them (0: more
+// than there is), and 16-byte granules of a span per lane.
+const SegWPlan kSegW[] = {{"w32", 1}, {"w64", 2}, {"w96", 3}, {"w128", 4}};
+constexpr int kSegWN = 4;
+constexpr int64_t kLds = 160 * 1024;
+constexpr int kSegWSmall = 4, kSegWLarge = 11;
+
+struct SegWDims {
+    int64_t nks, pitch, segb, lds, grans;
+};
+
+SegWDims segw_dims(const Shape &sh, int wm)
+{
+    SegWDims d;
+    d.nks = (sh.K + 15) / 16;
+    d.pitch = d.nks * 32 + 16;  // 32*nks is an even number of chunks
+    const int64_t npx = sh.Wo < 32 ? sh.Wo : 32;
+    const int64_t span = round_up(((npx - 1) * sh.S + 16 * d.nks) * 2, 16);
+    d.grans = (span / 16 + 63) / 64;
+    // a pixel past the strip's last one reads from the area's other bytes:
+    // 32 pixels' worth of them exist in every area
+    const int64_t full = round_up((31 * sh.S + 16 * d.nks) * 2 + 4, 16);
+    const int64_t stage = 32 * (64 * wm + 16);
+    d.segb = full > stage ? full : stage;
+    d.lds = 32 * wm * d.pitch + kSegWWaves * d.segb;
+    return d;
+}
+
+template <class E, int WM, int NG, int WPE>
+const void *segw_al(const Shape &sh)
+{
+    return sh.S * 2 % 8 == 0   ? (const void *)&conv_fp16_segw<E, WM, NG, 8, WPE>
+           : sh.S * 2 % 4 == 0 ? (const void *)&conv_fp16_segw<E, WM, NG, 4, WPE>
+                               : (const void *)&conv_fp16_segw<E, WM, NG, 2, WPE>;
+}
+
+template <class E, int WM>
+const void *segw_fn(const Shape &sh, const SegWDims &d)
+{
+    return d.grans <= kSegWSmall ? segw_al<E, WM, kSegWSmall, WM <= 2 ? 4 : 2>(sh) : segw_al<E, WM, kSegWLarge, 2>(sh);
+}
+
+template <class E>
+const void *segw_fn(const Shape &sh, int wm, const SegWDims &d)
+{
+    return wm == 1 ? segw_fn<E, 1>(sh, d) : wm == 2 ? segw_fn<E, 2>(sh, d) : wm == 3 ? segw_fn<E, 3>(sh, d)
+                                                                                    : segw_fn<E, 4>(sh, d);
+}
+
+bool segw_fits(const Shape &sh, int w)
+{
+    const SegWDims d = segw_dims(sh, kSegW[w].wm);
+    return sh.Ci % 8 != 0 && sh.d == 1 && d.grans <= kSegWLarge && d.lds <= kLds;
+}
+
+hipError_t launch_segw(const Shape &sh, int w, const void *ws, const uint16_t *filt, uint16_t *out, hipStream_t st,
+                       Op16 op)
+{
+    const int wm = kSegW[w].wm;
+    const SegWDims d = segw_dims(sh, wm);
+    SegWArgs a;
+    a.ws = static_cast<const uint16_t *>(ws);
+    a.filt = filt;
+    a.out = out;
+    a.K = (uint32_t)sh.K; a.Co = (uint32_t)sh.Co; a.Wo = (uint32_t)sh.Wo;
+    a.Ci = (uint32_t)sh.Ci; a.Kh = (uint32_t)sh.Kh; a.Kw = (uint32_t)sh.Kw; a.S = (uint32_t)sh.S;
+    a.L = (uint64_t)sh.L;
+    a.wps = (uint32_t)((sh.Wo + 31) / 32);
+    a.nblk = (uint32_t)(sh.strips * a.wps);  // at most P
+    a.nks = (uint32_t)d.nks; a.pitch = (uint32_t)d.pitch; a.segb = (uint32_t)d.segb;
+    a.div_wps = make_fastdiv(a.wps);
+    a.div_khci = make_fastdiv(a.Kh * a.Ci);
+    a.div_ci = make_fastdiv(a.Ci);
+    const void *f = op == Op16::BF16 ? segw_fn<BF16Op>(sh, wm, d) : segw_fn<F16Op>(sh, wm, d);
+    int dev = 0, cus = 0, per_cu = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess)
+        e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)d.lds);
+    if (e == hipSuccess)
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, 64 * kSegWWaves, (size_t)d.lds);
+    if (e != hipSuccess)
+        return e;
+    // one resident round of workgroups over the channel groups
+    const int64_t gy = (sh.Co + 32 * wm - 1) / (32 * wm), need = ((int64_t)a.nblk + kSegWWaves - 1) / kSegWWaves;
+    int64_t gx = (int64_t)(cus > 0 ? cus : 1) * (per_cu > 0 ? per_cu : 1) / gy;
+    gx = gx < 1 ? 1 : gx > need ? need : gx;
+    void *args[] = {&a};
+    return hipLaunchKernel(f, dim3((uint32_t)gx, (uint32_t)gy), dim3(64 * kSegWWaves), args, (size_t)d.lds, st);
+}
+
 }  // namespace
 
+// Variants of the tiled kernel, then the one-wave kernel's by channels.
 int seg_find(const char *name)
 {
     int n;
@@ -354,19 +664,32 @@ int seg_find(const char *name)
     for (int t = 0; t < n; ++t)
         if (strcmp(name, v[t].name) == 0)
             return t;
+    for (int t = 0; t < kSegWN; ++t)
+        if (strcmp(name, kSegW[t].name) == 0)
+            return n + t;
     return -1;
 }
 
 const char *seg_name(int v)
 {
     int n;
-    return seg_variants(&n)[v].name;
+    const SegVariant *t = seg_variants(&n);
+    return v < n ? t[v].name : kSegW[v - n].name;
+}
+
+bool seg_reads_filter(int v)
+{
+    int n;
+    seg_variants(&n);
+    return v >= n;
 }
 
 bool seg_fits(const Shape &sh, int pick)
 {
     int n;
     const SegVariant *v = seg_variants(&n);
+    if (pick >= n && pick < n + kSegWN)
+        return segw_fits(sh, pick - n);
     if (pick < 0 || pick >= n)
         return false;
     if (sh.d != 1)
@@ -388,6 +711,35 @@ int seg_default(const Shape &sh)
 {
     if (sh.Ci % 8 == 0)
         return -1;  // 16-byte-aligned windows have their own kernels
+    // The one-wave kernel wherever its filter rows and spans fit LDS (strips
+    // of at least 8 pixels, a quarter of a block), conv call in us against
+    // the tiled or register-staged kernel, each with its pack: 11x11 stride 4
+    // 3 -> 96 at 227x227 76 -> 50, 7x7 stride 2 3 -> 64 at 227x227 115 -> 74
+    // (16 images 20.8 -> 16.7), 5x5 stride 2 3 -> 96 37.6 -> 20.6; 3x3 52 ->
+    // 51 at 81x81, 92 images, 253 -> 76; 5x5 25 -> 273 at 34x34 80 -> 54; 1x1
+    // 100 -> 100 at 28x28 34.9 -> 25.3; 3x3 70 -> 150 at 14x14 29.5 -> 13.2.
+    // A block costs about 3 + wm for wm 32-channel rows (reading its span and
+    // storing it, against its matrix steps), so: few channel groups, little
+    // padding, and enough blocks for the 2048 waves.
+    if (sh.Wo >= 8) {
+        int n, best = -1;
+        int64_t least = 0;
+        seg_variants(&n);
+        const int64_t nblk = sh.strips * ((sh.Wo + 31) / 32);
+        for (int w = 0; w < kSegWN; ++w) {
+            if (!segw_fits(sh, w))
+                continue;
+            const int64_t groups = (sh.Co + 32 * kSegW[w].wm - 1) / (32 * kSegW[w].wm);
+            const int64_t blocks = nblk * groups < 2048 ? 2048 : nblk * groups;
+            const int64_t cost = blocks * (3 + kSegW[w].wm);
+            if (best < 0 || cost < least) {
+                best = n + w;
+                least = cost;
+            }
+        }
+        if (best >= 0)
+            return best;
+    }
     // C_o <= 64: 64 x 128 tiles with a 16 KiB segment area when the
     // segments fit it (five workgroups per CU instead of two: 7x7 s2 C_i=3
     // at 227x227 284 vs 245 TFLOP/s, 3x3 C_i=3 at 224x224 83 vs 79)
@@ -397,11 +749,14 @@ int seg_default(const Shape &sh)
     return seg_fits(sh, pick) ? pick : -1;
 }
 
-hipError_t launch_conv_fp16_seg(const Shape &sh, int plan, const void *ws, const void *packed,
+hipError_t launch_conv_fp16_seg(const Shape &sh, int plan, const void *ws, const uint16_t *filt, const void *packed,
                                 uint16_t *out, hipStream_t st, Op16 op)
 {
     int n;
-    const SegVariant &v = seg_variants(&n)[plan];
+    const SegVariant *t = seg_variants(&n);
+    if (plan >= n)
+        return launch_segw(sh, plan - n, ws, filt, out, st, op);
+    const SegVariant &v = t[plan];
     SegArgs a;
     a.ws = static_cast<const uint16_t *>(ws);
     a.packed = static_cast<const uint16_t *>(packed);
