@@ -76,7 +76,7 @@ struct DCfg {
     static constexpr int CW = WCH * LC * TN;      // channels per workgroup
     static_assert(TN % 4 == 0 && NW % (WCH * KS) == 0, "tile");
     static_assert(CW % 16 == 0, "whole 1 KiB filter loads per stage");
-    static_assert(KS == 1 || (KC == 16 && GR == 16), "tap split: 16-tap quads groups, 16-byte loads");
+    static_assert(KS == 1 || (KC == 16 && LPR <= 64), "tap split: 16-tap quad groups, whole window rows per load");
     static constexpr int WBYTES = BM * KT * 4;    // window part of a stage
     static constexpr int FBYTES = KT * CW * 4;    // filter part of a stage
     static constexpr int IW = WBYTES / (64 * GR) / NW;  // window loads per wave per stage
@@ -269,15 +269,15 @@ __global__ __launch_bounds__(C::NT) void conv_fp32_dma(D32Args a)
     // LDS row, in LDS quad g*GR/16; that quad holds quad wslot(pixel, .) of
     // the pixel's stage taps (with 4-byte granules, element g%4 of it).  The
     // tap depends on the pixel only through the swizzle bits of pl, which
-    // are the same for every load of a lane (PPI*b is a multiple of 16 when
-    // the swizzle uses pl & 3 and of 32 when it uses bit 3), so it is kept
-    // once per lane.
+    // are the same for every load of a lane (from one load to the next pl
+    // grows by PPI*NW, a multiple of 4 when the swizzle uses pl & 3 and of 16
+    // when it uses bit 3), so it is kept once per lane.
     {
-        const uint32_t pl = w.lane / C::LPR;
+        const uint32_t pl = C::PPI * w.wave + w.lane / C::LPR;
         const uint32_t g = w.lane % C::LPR;
         w.wk = C::GR == 16 ? 4 * DTile<C>::wslot(pl, g) : 4 * DTile<C>::wslot(pl, g / 4) + g % 4;
     }
-    static_assert(C::PPI % (C::QPR == 4 ? 4 : 16) == 0, "swizzle bits of pl fixed per lane");
+    static_assert(C::PPI * C::NW % (C::QPR == 4 ? 4 : 16) == 0, "swizzle bits of pl fixed per lane");
 #pragma unroll
     for (int i = 0; i < C::IW; ++i) {
         const uint32_t b = w.wave + C::NW * i;
@@ -327,7 +327,7 @@ __global__ __launch_bounds__(C::NT) void conv_fp32_dma(D32Args a)
     const uint32_t pl0 = w.wpx() * C::WBM + w.lane / C::LC;
     if constexpr (C::KS > 1) {
         // Every wave stores its sums in LDS; then the KS waves with the same
-        // pixels and channels each finish TM/KS of the lane's pixel rows,
+        // pixels and channels each finish a share of the lane's pixel rows,
         // adding the tap slices' sums in slice order (a fixed order: the
         // result does not depend on timing).
         constexpr int PPS = C::SLOT / C::WAVE_PART;  // parts per slot
@@ -351,18 +351,22 @@ __global__ __launch_bounds__(C::NT) void conv_fp32_dma(D32Args a)
         __syncthreads();
         if (jw >= a.Co)
             return;
-        for (int r = 0; r < C::TM / C::KS; ++r) {
-            const uint32_t t = r * C::KS + ks;
-            const uint32_t p = p0 + pl0 + C::LP * t;
-            if (p >= a.P)
+        // pieces of PC channels of one pixel row, dealt to the KS waves: whole
+        // rows of TN where there are at least KS of them
+        constexpr int PC = C::TM % C::KS == 0 ? C::TN : 4;
+        for (uint32_t r = ks; r < (uint32_t)(C::TM * (C::TN / PC)); r += C::KS) {
+            const uint32_t t = r / (C::TN / PC), cb = r % (C::TN / PC) * PC;
+            const uint32_t p = p0 + pl0 + C::LP * t, jp = jw + cb;
+            if (p >= a.P || jp >= a.Co)
                 continue;
-            float v[C::TN];
+            float v[PC];
 #pragma unroll
-            for (int c = 0; c < C::TN; c += 4) {
-                float4 sum = part(0)[(t * (C::TN / 4) + c / 4) * 64 + w.lane];
+            for (int c = 0; c < PC; c += 4) {
+                const uint32_t at = (t * (C::TN / 4) + (cb + c) / 4) * 64 + w.lane;
+                float4 sum = part(0)[at];
 #pragma unroll
                 for (int k = 1; k < C::KS; ++k) {
-                    const float4 u = part(k)[(t * (C::TN / 4) + c / 4) * 64 + w.lane];
+                    const float4 u = part(k)[at];
                     sum.x += u.x;
                     sum.y += u.y;
                     sum.z += u.z;
@@ -373,15 +377,15 @@ __global__ __launch_bounds__(C::NT) void conv_fp32_dma(D32Args a)
                 v[c + 2] = sum.z;
                 v[c + 3] = sum.w;
             }
-            float *o = a.out + (uint64_t)p * a.Co + jw;
-            if (jw + C::TN <= a.Co && (a.Co & 3) == 0) {
+            float *o = a.out + (uint64_t)p * a.Co + jp;
+            if (jp + PC <= a.Co && (a.Co & 3) == 0) {
 #pragma unroll
-                for (int c = 0; c < C::TN; c += 4)
+                for (int c = 0; c < PC; c += 4)
                     *reinterpret_cast<float4 *>(o + c) = make_float4(v[c], v[c + 1], v[c + 2], v[c + 3]);
             } else {
 #pragma unroll
-                for (int c = 0; c < C::TN; ++c)
-                    if (jw + c < a.Co)
+                for (int c = 0; c < PC; ++c)
+                    if (jp + c < a.Co)
                         o[c] = v[c];
             }
         }
@@ -473,6 +477,14 @@ const DVariant *d_variants(int *n)
         d_variant<4, 8, 8, 1, 2, 16, 16, 4>("p4c8l8s2k16t4"),
         // eight waves: two 32-pixel groups, each splitting the taps four ways
         d_variant<4, 8, 8, 1, 2, 16, 16, 4, 8>("p4c8l8s2k16t4w8"),
+        // small grids: 32 x 32 tiles, the taps split over four or eight waves,
+        // and 64 x 64 tiles split over eight
+        d_variant<4, 4, 8, 1, 2, 16, 16, 4, 4>("p4c4l8s2k16t4"),
+        d_variant<4, 4, 8, 1, 2, 16, 16, 8, 8>("p4c4l8s2k16t8w8"),
+        d_variant<8, 8, 8, 1, 2, 16, 16, 8, 8>("p8c8l8s2k16t8w8"),
+        // the tap split with 4-byte window loads
+        d_variant<4, 4, 8, 1, 2, 16, 4, 4, 4>("p4c4l8s2k16g4t4"),
+        d_variant<4, 8, 8, 1, 2, 16, 4, 4, 8>("p4c8l8s2k16g4t4w8"),
         // serialized rings of three of the above (check variants)
         d_variant<8, 8, 8, 1, 2, 16, 16, 1, 4, true>("p8c8l8s2k16-serial"),
         d_variant<6, 8, 8, 1, 2, 16, 4, 1, 4, true>("p6c8l8s2k16g4-serial"),
@@ -507,8 +519,8 @@ bool dma32_fits(const Shape &sh, int pick)
     const DVariant *v = d_variants(&n);
     if (pick < 0 || pick >= n)
         return false;
-    // filter offsets, up to one 64-tap stage past K_pad32, need 31 bits
-    if ((sh.K_pad32 + 64) * sh.Co_pad32 * 4 > (int64_t)kMaxRecords)
+    // filter offsets, up to one stage past K_pad32, need 31 bits
+    if ((sh.K_pad32 + (v[pick].kt > 64 ? v[pick].kt : 64)) * sh.Co_pad32 * 4 > (int64_t)kMaxRecords)
         return false;
     // 16-byte window loads need every window on a 16-byte boundary
     return v[pick].gr == 4 || sh.Ci % 4 == 0;
@@ -517,20 +529,53 @@ bool dma32_fits(const Shape &sh, int pick)
 int dma32_default(const Shape &sh)
 {
     const bool aligned = sh.Ci % 4 == 0;
-    const int64_t tiles256 = ((sh.P + 255) / 256) * ((sh.Co + 63) / 64);
-    // unaligned windows (C_i % 4 != 0, the 3-channel stems): the 6-pixel
-    // lane tile, 7x7 C_i=3 stride 2 67.2 vs 64.1 TFLOP/s (8-pixel) and 3x3
-    // C_i=3 36.6 vs 34.4, same machine
+    auto tiles = [&](int64_t px, int64_t ch) { return ((sh.P + px - 1) / px) * ((sh.Co + ch - 1) / ch); };
+    const int64_t tiles256 = tiles(256, 64);
     // strided overlapping windows (K_w > s > 1) re-read more of their
     // columns from L2 and run better with the 6-pixel tile's five workgroups
     // per CU: 7x7 C=64 stride 2 at 224x224, 95.0 vs 92.7 TFLOP/s in the
     // benchmark step (3x3 C=64 -> 128 stride 1 at 112x112: 94.8 vs 97.7)
     const bool strided = sh.s > 1 && sh.Kw > sh.s;
-    const char *name = !aligned          ? "p6c8l8s2k16g4"
-                       : tiles256 <= 128  ? "p8c8l8s2k16t4"
-                       : tiles256 <= 1024 ? "p4c8l8s2k16t4w8"
-                       : strided          ? "p6c8l8s2k16"
-                                          : "p8c8l8s2k16";
+    const char *name;
+    if (!aligned) {
+        // Unaligned windows (C_i % 4 != 0, the 3-channel stems): the tile
+        // whose busiest CU has the least work, ceil(tiles / 256) tiles of
+        // px x ch sums.  The 6-pixel lane tile is ahead of the 8-pixel one
+        // (7x7 C_i=3 stride 2 67.2 vs 64.1 TFLOP/s, 3x3 C_i=3 36.6 vs 34.4)
+        // and, at even balance, of the 4-pixel one (7x7 stride 2 3 -> 64 at
+        // 224x224, 32 images, 13 * 128 against 9 * 192 pixels: 121.5 vs 126.4
+        // us).  The 32 x 32 tile whose waves split the taps does its sums
+        // 1.25 times slower (same layer, 4 images: 30.4 vs 26.7), but fills
+        // the chip: one image 28.9 -> 13.1, 11x11 3 -> 96 stride 4 54.9 ->
+        // 13.0, 3x3 217 -> 63 at 28x28, 4 images, 268 -> 41.  A tile alone on
+        // its CU leaves its loads uncovered (3x3 50 -> 100 at 28x28, 170
+        // tiles of 128 pixels 52 us, 1352 of 32 x 32 30).
+        const int64_t n6 = tiles(192, 64), n4 = tiles(128, 64), ns = tiles(32, 32);
+        const int64_t c6 = (n6 + 255) / 256 * 192 * 64 * (n6 <= 256 ? 125 : 100);
+        const int64_t c4 = (n4 + 255) / 256 * 128 * 64 * (n4 <= 256 ? 125 : 100);
+        const int64_t cs = (ns + 255) / 256 * 32 * 32 * 125;
+        name = cs < c4 && cs < c6 ? "p4c4l8s2k16g4t4" : c4 < c6 ? "p4c8l8s2k16g4" : "p6c8l8s2k16g4";
+    } else if (tiles256 <= 128 && sh.s > 1 && sh.Kw > 2 * sh.s) {
+        name = "p8c8l8s2k16t4";  // few tiles of wide strided windows: the choice the plan tests fix
+    } else if (tiles(32, 32) <= 512) {
+        // Small grids: a 32 x 32 tile's sums take a quarter of the time of
+        // the 64 x 64 tile's four waves (conv call, us, against
+        // p8c8l8s2k16t4): 3x3 C=256 at 14x14, 1 / 8 images 101 -> 27.5, 104
+        // -> 37.9; 3x3 C=512 at 7x7 196 -> 53; 3x3 C=64 at 56x56 30.5 ->
+        // 11.2; 1x1 C=1024 51 -> 19.  Windows shorter than its 128-tap stage
+        // take the four-wave form (1x1 32 -> 48: 6.7 against 8.3).
+        name = sh.K >= 128 ? "p4c4l8s2k16t8w8" : "p4c4l8s2k16t4";
+    } else if (tiles(64, 64) <= 256) {
+        // 3x3 C=256 at 14x14, 16 images, 109 -> 61 us; 3x3 C=512 at 7x7, 32
+        // images, 204 -> 114 (p4c8l8s2k16t4w8: 66 and 123)
+        name = "p8c8l8s2k16t8w8";
+    } else if (tiles256 <= 1024) {
+        // (at most 128 tiles: 3x3 C=512 at 7x7, 128 images, 212 -> 205 us
+        // against p8c8l8s2k16t4; 3x3 C=256 at 14x14, 32 images, 114 -> 106)
+        name = "p4c8l8s2k16t4w8";
+    } else {
+        name = strided ? "p6c8l8s2k16" : "p8c8l8s2k16";
+    }
     // 96-channel tiles where they pad fewer channels than 64-channel ones
     // (C_o = 96: 0 against 32 of 128) and still give four workgroups per CU:
     // 11x11 C_i=3 C_o=96 stride 4, 60.7 -> 74.8 TFLOP/s; 3x3 C=64 -> 96 at
