@@ -903,16 +903,20 @@ int pipe_default(const Shape &sh)
     // C_o that fills 64-channel rows much better than 128-channel ones (144:
     // 192 against 256; 7x7 64 -> 144 dilated 47.4 vs 34.5)
     const bool half = round_up(sh.Co, 128) * 4 > round_up(sh.Co, 64) * 5;
-    // 256 x 128 over eight waves, three slots, one workgroup per CU: half
-    // again fewer bytes per FLOP than 128 x 128, so long windows run faster
-    // where the grid comes out at whole rounds of the CUs
-    const bool wide = sh.Co >= 256 && sh.K >= 1024 && rows_fit(sh, 256);
+    // 256 x 128 over eight waves, three slots, one workgroup per CU: a
+    // quarter fewer bytes per FLOP than 128 x 128, but nothing runs beside its
+    // first loads and its stores, so only for windows of 32 stages and more
+    // (1x1 C=1024 at 16x16, 96 images, 16 stages: 75.9 vs 68.9 with one-slot
+    // 128 x 128 tiles)
+    const bool wide = sh.Co >= 256 && sh.K >= 2048 && rows_fit(sh, 256);
     if (sh.Co <= 32)
         return pipe_find("c32p128s3");
     if (fp16_single_slot_rows(sh)) {
-        // 3x3 stride 2 C=256 at 56x56, 128 images (729 tiles, 2.85 rounds)
-        // 139 vs 130; 3x3 C=256 at 28x28 (784 tiles, 3.06 rounds) 134 vs 152
-        if (wide && t256 * 10 >= (t256 + 255) / 256 * 256 * 9)
+        // strided overlapping windows, whose reads the larger tile cuts most,
+        // at nearly whole rounds of the CUs: 3x3 stride 2 C=256 at 56x56, 128
+        // images (729 tiles, 2.85 rounds), 139 vs 130 (5x5 stride 1 at 28x28,
+        // 784 tiles: 362 vs 368)
+        if (wide && sh.s > 1 && sh.Kw > sh.s && t256 * 10 >= (t256 + 255) / 256 * 256 * 9)
             return pipe_find("c256p128s3w8");
         return pipe_find("c128p128s1");
     }
