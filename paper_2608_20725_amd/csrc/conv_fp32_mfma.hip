@@ -81,10 +81,13 @@ __global__ __launch_bounds__(256) void pack_filter_fp32_mfma(P32Args a)
     }
 }
 
-template <int WM_, int WN_, int WGM_, int WGN_, int NS_>
+// KS: the waves of a tile split the taps of every stage (each takes one of the
+// four chunk pairs, and their sums are added through LDS at the end).
+template <int WM_, int WN_, int WGM_, int WGN_, int NS_, int KS_ = 1>
 struct MCfg {
-    static constexpr int WM = WM_, WN = WN_, WGM = WGM_, WGN = WGN_, NS = NS_;
-    static constexpr int NW = WGM * WGN, NT = 64 * NW;
+    static constexpr int WM = WM_, WN = WN_, WGM = WGM_, WGN = WGN_, NS = NS_, KS = KS_;
+    static_assert(KS == 1 || KS == BK / 8, "one chunk pair per wave, or all");
+    static constexpr int NW = WGM * WGN * KS, NT = 64 * NW;
     static constexpr int BM = 32 * WM * WGM;     // channels per workgroup
     static constexpr int BN = 32 * WN * WGN;     // pixels per workgroup
     static constexpr int ROWS = BM + BN;
@@ -92,8 +95,11 @@ struct MCfg {
     static constexpr int BLOCKS = ROWS / 8;      // 1 KiB (8-row) blocks per stage
     static_assert(BLOCKS % NW == 0, "blocks split evenly over the waves");
     static constexpr int I = BLOCKS / NW;        // loads per wave per stage
-    static_assert(NS >= 2 && NS <= 3, "ring depth");
+    static_assert(NS >= 2 && NS <= 4, "ring depth");
     static_assert((NS - 2) * I <= 63, "vmcnt range");
+    static constexpr int PART = WM * WN * 4096;  // bytes of a wave's sums
+    static constexpr int PPS = STAGE / PART;     // such parts per slot
+    static_assert(KS == 1 || (WGM * WGN == 1 && NS * PPS >= KS), "the waves' sums fit the ring");
 };
 
 template <int VM>
@@ -153,6 +159,17 @@ struct MTile {
     __device__ inline void compute(const char *slot)
     {
         floatx4 af[2][C::WM], bf[2][C::WN];
+        if constexpr (C::KS > 1) {
+            frags(slot, (int)wave, af[0], bf[0]);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int i = 0; i < C::WM; ++i)
+#pragma unroll
+                    for (int j = 0; j < C::WN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[0][i][t], bf[0][j][t], acc[i][j], 0, 0, 0);
+            return;
+        }
         frags(slot, 0, af[0], bf[0]);
 #pragma unroll
         for (int g = 0; g < BK / 8; ++g) {
@@ -186,17 +203,18 @@ struct MTile {
 template <class C>
 __global__ __launch_bounds__(C::NT) void conv_fp32_mfma(M32Args a)
 {
-    constexpr int S2 = C::NS > 2 ? C::STAGE : 1024;
+    constexpr int S2 = C::NS > 2 ? C::STAGE : 1024, S3 = C::NS > 3 ? C::STAGE : 1024;
     __shared__ __attribute__((aligned(1024))) char r0[C::STAGE];
     __shared__ __attribute__((aligned(1024))) char r1[C::STAGE];
     __shared__ __attribute__((aligned(1024))) char r2[S2];
+    __shared__ __attribute__((aligned(1024))) char r3[S3];
     // Window offsets of the tile's pixels, in the slot that is loaded last (the
     // first load into it follows a barrier that follows every read of them):
     // an array of its own would take the 64 x 256 tile past half of the
     // 160 KiB LDS, one workgroup per CU instead of two (7x7 C=64 stride 2 at
     // 224x224: 5204 us vs 4761 together
     // with the column order of launch_conv_fp32_mfma).
-    uint32_t *const rowoff = reinterpret_cast<uint32_t *>(C::NS > 2 ? r2 : r1);
+    uint32_t *const rowoff = reinterpret_cast<uint32_t *>(C::NS > 3 ? r3 : C::NS > 2 ? r2 : r1);
 
     MTile<C> w;
     const uint32_t tid = threadIdx.x;
@@ -206,7 +224,8 @@ __global__ __launch_bounds__(C::NT) void conv_fp32_mfma(M32Args a)
     w.K = a.K;
     w.to = a.to;
     w.nst = a.K_pad / BK;
-    const uint32_t wm = w.wave / C::WGN, wn = w.wave % C::WGN;
+    const uint32_t wt = C::KS > 1 ? 0u : w.wave;  // with the taps split, every wave has the whole tile
+    const uint32_t wm = wt / C::WGN, wn = wt % C::WGN;
     uint32_t tx, ty;
     a.tg.tile(tx, ty);
     const uint32_t p0 = tx * C::BN;
@@ -264,15 +283,75 @@ __global__ __launch_bounds__(C::NT) void conv_fp32_mfma(M32Args a)
             w.step(st, r0, r1);
             w.step(st + 1, r1, r0);
         }
-    } else {
+    } else if constexpr (C::NS == 3) {
         w.issue(1, r1);
         for (uint32_t st = 0; st < w.nst; st += 3) {
             w.step(st, r0, r2);
             w.step(st + 1, r1, r0);
             w.step(st + 2, r2, r1);
         }
+    } else {
+        w.issue(1, r1);
+        w.issue(2, r2);
+        for (uint32_t st = 0; st < w.nst; st += 4) {
+            w.step(st, r0, r3);
+            w.step(st + 1, r1, r0);
+            w.step(st + 2, r2, r1);
+            w.step(st + 3, r3, r2);
+        }
     }
     wait_vmcnt<0>();  // no load may still be writing LDS when the workgroup ends
+
+    if constexpr (C::KS > 1) {
+        // the waves' sums as 16-byte quads [block][quad][lane], PPS parts per
+        // ring slot; wave q then adds quad q of every block in wave order and
+        // stores it
+        __syncthreads();
+        auto part = [&](uint32_t k) {
+            const uint32_t s = k / C::PPS;
+            char *slot = s == 0 ? r0 : s == 1 ? r1 : r2;
+            if constexpr (C::NS > 3)
+                slot = s == 3 ? r3 : slot;
+            return reinterpret_cast<float4 *>(slot + k % C::PPS * C::PART);
+        };
+        float4 *mine = part(w.wave);
+#pragma unroll
+        for (int i = 0; i < C::WM; ++i)
+#pragma unroll
+            for (int j = 0; j < C::WN; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    mine[((i * C::WN + j) * 4 + q) * 64 + w.lane] =
+                        make_float4(w.acc[i][j][4 * q], w.acc[i][j][4 * q + 1], w.acc[i][j][4 * q + 2],
+                                    w.acc[i][j][4 * q + 3]);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < C::WM; ++i)
+#pragma unroll
+            for (int j = 0; j < C::WN; ++j) {
+                const uint32_t at = ((i * C::WN + j) * 4 + w.wave) * 64 + w.lane;
+                float4 s = part(0)[at];
+#pragma unroll
+                for (uint32_t k = 1; k < 4; ++k) {
+                    const float4 v = part(k)[at];
+                    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+                }
+                const uint32_t p = p0 + 32 * j + (w.lane & 31), c = ch0 + 32 * i + 8 * w.wave + 4 * (w.lane >> 5);
+                if (p >= a.P)
+                    continue;
+                float *o = a.out + (uint64_t)p * a.Co + c;
+                if (c + 3 < a.Co && (a.Co & 3) == 0) {
+                    *reinterpret_cast<float4 *>(o) = s;
+                } else {
+                    const float v[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (c + e < a.Co)
+                            o[e] = v[e];
+                }
+            }
+        return;
+    }
 
     // Lane holds pixel pb + 32*j + (lane & 31) and, for accumulator element e
     // of block (i, j), channel cb + 32*i + 8*(e/4) + 4*(lane/32) + e%4: four
@@ -310,10 +389,10 @@ struct MVariant {
     int bm, bn, nt;
 };
 
-template <int WM, int WN, int WGM, int WGN, int NS>
+template <int WM, int WN, int WGM, int WGN, int NS, int KS = 1>
 MVariant m_variant(const char *name)
 {
-    using C = MCfg<WM, WN, WGM, WGN, NS>;
+    using C = MCfg<WM, WN, WGM, WGN, NS, KS>;
     return MVariant{name, (const void *)&conv_fp32_mfma<C>, C::BM, C::BN, C::NT};
 }
 
@@ -327,6 +406,10 @@ const MVariant *m_variants(int *n)
         // smaller tiles for layers with few output pixels
         m_variant<1, 2, 2, 2, 2>("c64p128s2"),
         m_variant<1, 1, 1, 4, 2>("c32p128s2"),
+        // the taps of a stage split over four waves (small grids)
+        m_variant<1, 1, 1, 1, 4, 4>("c32p32s4t4"),
+        m_variant<1, 1, 1, 1, 2, 4>("c32p32s2t4"),
+        m_variant<2, 1, 1, 1, 4, 4>("c64p32s4t4"),
     };
     *n = (int)(sizeof v / sizeof v[0]);
     return v;
@@ -376,7 +459,12 @@ int mfma32_default(const Shape &sh)
     // tiles 1880, 32 x 128 1977, 32 x 256 2031).  Against the largest tile
     // with two workgroups per CU: 3x3 C=512 at 14x14 (576 / 2304 tiles) 848 ->
     // 713 us, 3x3 C=256 at 14x14 226 -> 207, 1x1 C=1024 at 14x14 457 -> 437.
-    static const int weight[] = {100, 103, 111, 103, 108};  // by variant
+    // The tiles whose waves split the taps fill the chip with the fewest
+    // pixels and come within 11 to 16 % of the large ones at even balance (3x3
+    // C=256 at 14x14, one image 55.6 -> 24.9, 128 images 207 -> 191; 3x3 C=512
+    // at 7x7, 128 images, 170 -> 157; 5x5 40 -> 88 at 42x42, 3 images, 28.4
+    // -> 17.5).
+    static const int weight[] = {100, 103, 111, 103, 108, 116, 114, 111};  // by variant
     int best = 0;
     int64_t least = -1;
     for (int i = 0; i < n; ++i) {
@@ -384,7 +472,9 @@ int mfma32_default(const Shape &sh)
         // one workgroup per CU leaves its barriers and load waits uncovered
         // (1x1 140 -> 313 at 18x18, 15 images: 190 tiles 17.7 us, 380 half as
         // large 16.2)
-        const int64_t alone = tiles <= 256 ? 106 : 100;
+        // (and the two-slot tap-split tile wants more than two per CU: 392
+        // tiles 36.3 against 33.2 with four slots, 1520 14.7 against 15.9)
+        const int64_t alone = i == 6 && tiles <= 512 ? 112 : tiles <= 256 ? 106 : 100;
         const int64_t cost = (tiles + 255) / 256 * v[i].bm * v[i].bn * weight[i] * alone;
         if (least < 0 || cost < least) {
             best = i;

@@ -51,3 +51,32 @@ def test_small_grid_tiles(shape, names, monkeypatch):
 ])
 def test_small_grid_defaults(shape, want):
     assert pkg.conv_im2win_kernel_name(*shape, torch.float32).split()[1] == want
+
+
+@pytest.mark.parametrize("shape", [(1, 4, 1, 1, 4, 1, 1, 1), (1, 32, 5, 7, 33, 1, 1, 1), (2, 36, 4, 9, 66, 1, 1, 1),
+                                   (2, 32, 11, 12, 100, 3, 3, 2), (3, 64, 9, 9, 31, 3, 3, 1), (1, 20, 9, 8, 7, 5, 5, 2)],
+                         ids=lambda v: "x".join(map(str, v)))
+def test_matrix_core_tap_split_tiles(shape, monkeypatch):
+    """fp32 on the matrix cores, the taps of a stage split over four waves:
+    windows of one chunk, one stage, and one chunk into a stage."""
+    N, Ci, H, W, Co, Kh, Kw, s = shape
+    x, w = workloads.draw(N, Ci, H, W, Co, Kh, Kw, 61)
+    xi, wi = workloads.draw(N, Ci, H, W, Co, Kh, Kw, 62, dist="int2")
+    ref = torch.from_numpy(oracle.conv(xi.double().numpy(), wi.double().numpy(), s)).float()
+
+    def conv(a, b):
+        r = Run(a, b, s, torch.float32, conv=False)
+        pkg.conv_im2win_fp32_mfma(r.ws, r.wd, r.out, r.N, r.Ci, r.H, r.W, s)
+        torch.cuda.synchronize()
+        return r
+
+    for name in ("c32p32s4t4", "c32p32s2t4", "c64p32s4t4"):
+        monkeypatch.setenv("IM2WIN_FP32_MFMA_TILE", name)
+        assert pkg.conv_im2win_kernel_name(*shape, "f32", fp32_matrix_cores=True) == "conv_fp32_mfma " + name
+        say("fp32 mfma split", name, shape)
+        r = conv(x, w)
+        check_full(r, x, w)
+        r.check_workspace_guard()
+        r.check_out_guards()
+        assert torch.equal(r.out.view(torch.int32), conv(x, w).out.view(torch.int32))
+        assert torch.equal(conv(xi, wi).out.cpu(), ref), name
