@@ -44,7 +44,6 @@ struct TArgs {
     uint64_t win_elems;
     uint64_t win_bytes, pad_end;
     uint64_t grans;          // gather: 16-byte granules of the window tensor
-    uint64_t in_pixels;      // pieces: pixels of the input (N * H_i * W_i)
     uint32_t cu;             // pieces: units per pixel
     uint32_t spb, segs, cpb; // pieces: strips per block; pieces per strip, columns per piece
     uint32_t xcd_order;      // vec, pieces: 1 = XCD-aware block order, 0 = linear (ablation)
@@ -129,16 +128,24 @@ __global__ __launch_bounds__(kThreads) void transform_vec(TArgs a)
 // position (image, strip, filter row) is the same for a whole wave, so a lane
 // adds little more than one LDS address per element.  Measured (us, 128
 // images unless said, element gather -> pieces): fp16 11x11 stride 4 at
-// 227x227 65 -> 40, 7x7 stride 2 80 -> 49, 3x3 at 224x224 64 -> 42; fp32 7x7
-// stride 2 pad 3 at 224x224, 32 images, 27.4 -> 18.6 (4.8 TB/s), 11x11 74 ->
-// 58; fp16 3x3 52 channels at 81x81, 92 images, 108 -> 38; and against the
-// one-load-per-pixel gather it replaces, fp32 3x3 at 224x224 67 -> 60.
+// 227x227 65 -> 26.4 (5.5 TB/s), 7x7 stride 2 80 -> 34, 3x3 at 224x224 64 ->
+// 24.5; fp32 7x7 stride 2 pad 3 at 224x224, 32 images, 27.4 -> 18.6 (4.8
+// TB/s), 11x11 74 -> 58; fp16 3x3 52 channels at 81x81, 92 images, 108 -> 38;
+// and against the one-load-per-pixel gather it replaces, fp32 3x3 at 224x224
+// 67 -> 60.
 //
 // The row is read as units of UB = 2, 4 or 8 bytes, the largest that divides
 // a pixel's C_i*elt bytes, V consecutive units per lane and load: 16 bytes (8
 // with 2-byte units), one unit for rows too short to fill a wave that way, or
-// three: one 3-channel pixel, which needs no carry into the next column.  Padding rows and columns are the zeros the piece starts
-// with.
+// one or two 3-channel pixels, which need no carry into the next column:
+// three 4-byte units, or six 2-byte ones, whose two pixels leave as one dword
+// and one half each.  Two pixels a lane against one, its three halves stored
+// one by one, took the 16-bit times above from 40, 47.5 and 41 us (LDS writes
+// and address arithmetic bound them), 7x7 stride 2 pad 3, 32 images, 18.4 ->
+// 12.5; with the input from HBM and a conv between, 11x11 52 -> 40.  Two such loads in flight need rows of more than 64 pairs to be of
+// use: with one, 32-wide images 8.3 -> 6.9, one 224-wide image cut into short
+// pieces 4.17 -> 3.94.  Padding rows and columns are the zeros the piece
+// starts with.
 template <int UB>
 struct UnitOf;
 template <>
@@ -150,11 +157,11 @@ struct UnitOf<8> { typedef uint64_t type; };
 
 constexpr uint32_t kPieceBytes = 16384;
 
-template <int UB, int V>
+// U: loads in flight per lane
+template <int UB, int V, int U = 4>
 __global__ __launch_bounds__(kThreads) void transform_pieces(TArgs a)
 {
     typedef typename UnitOf<UB>::type unit;
-    constexpr int U = 4;  // loads in flight per lane
     __shared__ uint4 buf[kPieceBytes / 16 + 2];
     char *lds = reinterpret_cast<char *>(buf);
 
@@ -188,41 +195,59 @@ __global__ __launch_bounds__(kThreads) void transform_pieces(TArgs a)
         const int32_t h = (int32_t)(m * a.s + u) - (int32_t)a.ph;
         if (h < 0 || h >= (int32_t)a.Hi)
             continue;
-        const uint64_t px = ((uint64_t)i * a.Hi + (uint32_t)h) * a.Wi + (v0 - a.pw);
-        const char *src = a.in + px * cu * UB;
+        const char *src = a.in + (((uint64_t)i * a.Hi + (uint32_t)h) * a.Wi + (v0 - a.pw)) * cu * UB;
         char *dst = lds + lead + (st * stripu + ((v0 - k0) * a.Kh + u) * cu) * UB;
-        if constexpr (V == 3) {
-            // the last row of the input: its last pixel's 8-byte load starts 2 bytes early
-            const bool end = UB == 2 && px + (v1 - v0) == a.in_pixels;
+        if constexpr (UB == 2 && V == 6) {
+            // columns k (even), k + 1 of a lane: whether their six bytes each
+            // start on a 4-byte boundary of LDS is the same for the whole wave
+            const uint32_t np = (v1 - v0) / 2, o0 = lead + (st * stripu + ((v0 - k0) * a.Kh + u) * 3) * 2;
+            const bool a0 = (o0 & 2) == 0, a1 = ((o0 + colu * 2) & 2) == 0;
+            for (uint32_t x = lane; x < np; x += 64 * U) {
+                uint32_t el[U][3];
+#pragma unroll
+                for (int t = 0; t < U; ++t) {
+                    // lanes past the row repeat its last pair
+                    const uint32_t p = x + 64 * t < np ? x + 64 * t : np - 1;
+                    __builtin_memcpy(el[t], src + p * 12u, 12);
+                }
+#pragma unroll
+                for (int t = 0; t < U; ++t) {
+                    const uint32_t p = x + 64 * t < np ? x + 64 * t : np - 1;
+                    char *o = dst + p * (colu * 4), *e = o + colu * 2;
+                    if (a0) {
+                        *reinterpret_cast<uint32_t *>(o) = el[t][0];
+                        *reinterpret_cast<uint16_t *>(o + 4) = (uint16_t)el[t][1];
+                    } else {
+                        *reinterpret_cast<uint16_t *>(o) = (uint16_t)el[t][0];
+                        *reinterpret_cast<uint32_t *>(o + 2) = __builtin_amdgcn_alignbyte(el[t][1], el[t][0], 2);
+                    }
+                    if (a1) {
+                        *reinterpret_cast<uint32_t *>(e) = __builtin_amdgcn_alignbyte(el[t][2], el[t][1], 2);
+                        *reinterpret_cast<uint16_t *>(e + 4) = (uint16_t)(el[t][2] >> 16);
+                    } else {
+                        *reinterpret_cast<uint16_t *>(e) = (uint16_t)(el[t][1] >> 16);
+                        *reinterpret_cast<uint32_t *>(e + 2) = el[t][2];
+                    }
+                }
+            }
+            // the last column of an odd number
+            if (((v1 - v0) & 1) && lane < 3) {
+                unit el;
+                __builtin_memcpy(&el, src + (np * 6 + lane) * UB, UB);
+                *reinterpret_cast<unit *>(dst + (2 * np * colu + lane) * UB) = el;
+            }
+        } else if constexpr (V == 3) {
             const uint32_t nk = v1 - v0;
             for (uint32_t x = lane; x < nk; x += 64 * U) {
                 unit el[U][3];
 #pragma unroll
-                for (int t = 0; t < U; ++t) {
-                    if constexpr (UB == 2) {
-                        // lanes past the row repeat its last pixel (a branch
-                        // per load measured 44.0 vs 41.0 us on 11x11 stride 4)
-                        const uint32_t k = x + 64 * t < nk ? x + 64 * t : nk - 1;
-                        const uint32_t adj = end && k == nk - 1 ? 2u : 0u;
-                        uint32_t v[2];
-                        __builtin_memcpy(v, src + (int32_t)(k * 6u - adj), 8);  // -2 for a row's only pixel
-                        if (end) {
-                            v[0] = adj ? __builtin_amdgcn_alignbyte(v[1], v[0], 2) : v[0];
-                            v[1] = adj ? v[1] >> 16 : v[1];
-                        }
-                        el[t][0] = (unit)v[0];
-                        el[t][1] = (unit)(v[0] >> 16);
-                        el[t][2] = (unit)v[1];
-                    } else if (x + 64 * t < nk) {
+                for (int t = 0; t < U; ++t)
+                    if (x + 64 * t < nk)
                         __builtin_memcpy(el[t], src + (x + 64 * t) * 12u, 12);
-                    }
-                }
 #pragma unroll
                 for (int t = 0; t < U; ++t) {
-                    uint32_t k = x + 64 * t;
-                    if (UB == 2)
-                        k = k < nk ? k : nk - 1;
-                    else if (k >= nk)
+                    const uint32_t k = x + 64 * t;
+                    if (k >= nk)
                         continue;
                     unit *o = reinterpret_cast<unit *>(dst + k * (colu * UB));
                     o[0] = el[t][0];
@@ -416,8 +441,7 @@ hipError_t launch_transform(const Shape &sh, const void *in, void *ws, hipStream
     // IM2WIN_TRANSFORM_KERNEL=pieces takes it wherever it can run, =gather
     // nowhere.
     const int64_t colb = sh.Kh * sh.Ci * sh.elt;
-    a.in_pixels = (uint64_t)sh.N * a.Hi * a.Wi;
-    if (sh.d == 1 && 2 * colb <= kPieceBytes && a.in_pixels > 1 && !t.transform_gather &&
+    if (sh.d == 1 && 2 * colb <= kPieceBytes && !t.transform_gather &&
         (t.transform_pieces || (sh.Ci > (sh.Kh > 1 ? 2 : 3) &&
                                 (int64_t)a.grans >= (sh.elt == 4 || sh.Kh == 1 ? 1 << 18 : 1 << 15)))) {
         // pieces of at most 16 KiB (eight blocks per CU), smaller ones while
@@ -448,7 +472,9 @@ hipError_t launch_transform(const Shape &sh, const void *in, void *ws, hipStream
         a.div_cu = make_fastdiv(a.cu);
         const bool narrow = cpb * a.cu <= 256;  // one unit per lane, U times, covers a row
         const void *f =
-            sh.Ci == 3 ? (sh.elt == 4 ? (const void *)&transform_pieces<4, 3> : (const void *)&transform_pieces<2, 3>)
+            sh.Ci == 3 ? (sh.elt == 4  ? (const void *)&transform_pieces<4, 3>
+                          : cpb <= 128 ? (const void *)&transform_pieces<2, 6, 1>
+                                       : (const void *)&transform_pieces<2, 6, 2>)
             : ub == 8  ? (narrow ? (const void *)&transform_pieces<8, 1> : (const void *)&transform_pieces<8, 2>)
             : ub == 4  ? (narrow ? (const void *)&transform_pieces<4, 1> : (const void *)&transform_pieces<4, 4>)
                        : (narrow ? (const void *)&transform_pieces<2, 1> : (const void *)&transform_pieces<2, 4>);

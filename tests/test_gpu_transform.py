@@ -161,3 +161,15 @@ def test_transform_pieces_equal_gather(case, dtype, monkeypatch):
         pkg.conv_im2win_transform_padded(xd, ws[:need], 2, Kh, Kw, s, ph, pw)
         outs.append(ws.cpu())
     assert torch.equal(outs[0], outs[1])
+
+
+# 16-bit 3-channel rows are read two pixels at a time: rows of one pixel, odd
+# ones, ones of just over 64 and 128 pairs, even and odd filter heights (the
+# six bytes of a pixel start on either half of a dword), pieces that start at
+# an odd column, inputs that end with the row.
+@pytest.mark.parametrize("case", [
+    (1, 3, 1, 1, 3, 1, 1, 1, 1), (1, 3, 4, 2, 4, 1, 1, 0, 0), (3, 3, 9, 131, 4, 2, 1, 0, 0), (2, 3, 5, 129, 5, 1, 1, 2, 2),
+    (2, 3, 12, 257, 3, 1, 1, 0, 1), (1, 3, 30, 701, 2, 1, 1, 0, 0), (40, 3, 40, 7, 3, 2, 1, 0, 0), (1, 3, 2, 3, 1, 1, 1, 5, 4),
+], ids=lambda s: "x".join(map(str, s)))
+def test_transform_pieces_pixel_pairs(case, monkeypatch):
+    test_transform_pieces_equal_gather(case, torch.float16, monkeypatch)
