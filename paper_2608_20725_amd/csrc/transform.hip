@@ -142,10 +142,11 @@ __global__ __launch_bounds__(kThreads) void transform_vec(TArgs a)
 // and one half each.  Two pixels a lane against one, its three halves stored
 // one by one, took the 16-bit times above from 40, 47.5 and 41 us (LDS writes
 // and address arithmetic bound them), 7x7 stride 2 pad 3, 32 images, 18.4 ->
-// 12.5; with the input from HBM and a conv between, 11x11 52 -> 40.  Two such loads in flight need rows of more than 64 pairs to be of
-// use: with one, 32-wide images 8.3 -> 6.9, one 224-wide image cut into short
-// pieces 4.17 -> 3.94.  Padding rows and columns are the zeros the piece
-// starts with.
+// 12.5; with the input from HBM and a conv between, 11x11 52 -> 40, transform
+// and conv together 104 -> 93, 7x7 147 -> 131, 3x3 199 -> 181.  Two such
+// loads in flight need rows of more than 64 pairs to be of use: with one,
+// 32-wide images 8.3 -> 6.9, one 224-wide image cut into short pieces 4.17 ->
+// 3.94.  Padding rows and columns are the zeros the piece starts with.
 template <int UB>
 struct UnitOf;
 template <>
