@@ -238,6 +238,20 @@ __device__ inline void ring_barrier()
     asm volatile("" ::: "memory");
 }
 
+// Hands LDS bytes from the lanes of a wave that wrote (or read) them to the
+// lanes of the same wave that read (or overwrite) them next.  A wave's LDS
+// operations execute in order; the fences hold the compiler to that order,
+// for which s_waitcnt and wave_barrier alone are no memory operations: it may
+// move an access past them whose address it can tell from the other lane's.
+// At wavefront scope they add no instruction and leave global loads in flight
+// (the kernels' machine code is the same with and without them).
+__device__ inline void wave_lds_handoff()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ inline uint32_t ld_b16(__amdgpu_buffer_rsrc_t r, uint32_t off)
 {
     return __builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, 0);

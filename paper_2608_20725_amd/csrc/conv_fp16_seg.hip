@@ -454,7 +454,7 @@ __global__ __launch_bounds__(64 * kSegWWaves, WPE) void conv_fp16_segw(SegWArgs 
                 *reinterpret_cast<u32x4 *>(area + off) = pre[g];
         }
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the wave's span is in LDS
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_handoff();
         if (blk + step < a.nblk)
             load(blk + step);
 
@@ -519,7 +519,7 @@ __global__ __launch_bounds__(64 * kSegWWaves, WPE) void conv_fp16_segw(SegWArgs 
 
         // round once, stage the block as [pixel][channel] in the wave's area,
         // and store whole output rows
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_handoff();
         const uint32_t q = fdiv(blk, a.div_wps), n0 = (blk - q * a.wps) * 32;
         const uint32_t npx = a.Wo - n0 < 32 ? a.Wo - n0 : 32;
 #pragma unroll
@@ -534,7 +534,7 @@ __global__ __launch_bounds__(64 * kSegWWaves, WPE) void conv_fp16_segw(SegWArgs 
                     make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
             }
         __builtin_amdgcn_s_waitcnt(0xC07F);
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_handoff();
         uint16_t *const o = a.out + ((uint64_t)q * a.Wo + n0) * a.Co + ch0;
 #pragma unroll
         for (int t = 0; t < 2 * WM; ++t) {
@@ -553,7 +553,7 @@ __global__ __launch_bounds__(64 * kSegWWaves, WPE) void conv_fp16_segw(SegWArgs 
             }
         }
         __builtin_amdgcn_s_waitcnt(0xC07F);  // the rows are read before the next span lands on them
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_handoff();
     }
 }
 

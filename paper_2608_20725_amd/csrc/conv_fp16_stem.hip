@@ -123,7 +123,7 @@ struct StemBlock {
             }
         // the wave's own LDS writes, read back below by other lanes
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_handoff();
         const uint32_t live = a.P - blk * 32 < 32 ? a.P - blk * 32 : 32;
         const uint32_t nch = a.Co / 8;  // 16-byte chunks per output row
         const uint32_t c = lane % NCHP, r0 = lane / NCHP;
@@ -142,7 +142,7 @@ struct StemBlock {
         }
         // every lane has read its chunks before the next block's rows land
         __builtin_amdgcn_s_waitcnt(0xC07F);
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_handoff();
     }
 };
 

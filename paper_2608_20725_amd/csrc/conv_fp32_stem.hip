@@ -107,7 +107,7 @@ __global__ __launch_bounds__(64 * kS32Waves) void conv_fp32_stem(S32Args a)
                 *reinterpret_cast<float4 *>(lds + lane * 32 + 4 * (k ^ (lane & 7))) =
                     make_float4(acc[4 * k], acc[4 * k + 1], acc[4 * k + 2], acc[4 * k + 3]);
             __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave's rows are in LDS
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_handoff();
             // instruction i: rows 8*i + lane/8, chunk lane%8 (channels
             // c0 + 4*(lane%8) ..): eight 128-byte line pieces of the output;
             // chunks past C_o read nothing (their offset is out of range)
@@ -120,7 +120,7 @@ __global__ __launch_bounds__(64 * kS32Waves) void conv_fp32_stem(S32Args a)
                                                        0, 0);
             }
             __builtin_amdgcn_s_waitcnt(0xC07F);  // reads done before the next rows land
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_handoff();
         }
     }
 }
