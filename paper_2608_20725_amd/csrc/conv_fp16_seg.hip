@@ -19,6 +19,7 @@
 #include "common.hpp"
 #include "epilogue16.hpp"
 
+#include <atomic>
 #include <type_traits>
 
 #include <stdlib.h>
@@ -590,25 +591,62 @@ SegWDims segw_dims(const Shape &sh, int wm)
     return d;
 }
 
+// Kernel instances by [32-channel rows][large spans][AL 8, 4, 2].
 template <class E, int WM, int NG, int WPE>
-const void *segw_al(const Shape &sh)
+const void *segw_al(int al)
 {
-    return sh.S * 2 % 8 == 0   ? (const void *)&conv_fp16_segw<E, WM, NG, 8, WPE>
-           : sh.S * 2 % 4 == 0 ? (const void *)&conv_fp16_segw<E, WM, NG, 4, WPE>
-                               : (const void *)&conv_fp16_segw<E, WM, NG, 2, WPE>;
+    return al == 0   ? (const void *)&conv_fp16_segw<E, WM, NG, 8, WPE>
+           : al == 1 ? (const void *)&conv_fp16_segw<E, WM, NG, 4, WPE>
+                     : (const void *)&conv_fp16_segw<E, WM, NG, 2, WPE>;
 }
 
 template <class E, int WM>
-const void *segw_fn(const Shape &sh, const SegWDims &d)
+const void *segw_fn(bool large, int al)
 {
-    return d.grans <= kSegWSmall ? segw_al<E, WM, kSegWSmall, WM <= 2 ? 4 : 2>(sh) : segw_al<E, WM, kSegWLarge, 2>(sh);
+    return large ? segw_al<E, WM, kSegWLarge, 2>(al) : segw_al<E, WM, kSegWSmall, WM <= 2 ? 4 : 2>(al);
 }
 
 template <class E>
-const void *segw_fn(const Shape &sh, int wm, const SegWDims &d)
+const void *segw_fn(int wm, bool large, int al)
 {
-    return wm == 1 ? segw_fn<E, 1>(sh, d) : wm == 2 ? segw_fn<E, 2>(sh, d) : wm == 3 ? segw_fn<E, 3>(sh, d)
-                                                                                    : segw_fn<E, 4>(sh, d);
+    return wm == 1   ? segw_fn<E, 1>(large, al)
+           : wm == 2 ? segw_fn<E, 2>(large, al)
+           : wm == 3 ? segw_fn<E, 3>(large, al)
+                     : segw_fn<E, 4>(large, al);
+}
+
+// Workgroups of instance f (number id) that are resident at once with `lds`
+// bytes of dynamic LDS.  The LDS limit is an attribute of the function, shared
+// by the layers and host threads that run it: it is set to the CU's whole LDS,
+// the same value whoever sets it, so that no thread lowers it between
+// another's query and launch.  The last answer of every instance and device is
+// kept (one 64-bit word: the LDS size and the workgroups for it), so that a
+// repeated call asks the driver for the device alone.
+hipError_t segw_resident(const void *f, int id, int64_t lds, int64_t *wgs)
+{
+    constexpr int kDevices = 64, kInstances = 2 * kSegWN * 2 * 3;
+    static std::atomic<uint64_t> kept[kDevices][kInstances];
+    int dev = 0, cus = 0, per_cu = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess)
+        return e;
+    std::atomic<uint64_t> *const slot = dev >= 0 && dev < kDevices ? &kept[dev][id] : nullptr;
+    const uint64_t k = slot ? slot->load(std::memory_order_acquire) : 0u;
+    if (k >> 32 == (uint64_t)lds) {
+        *wgs = (int64_t)(k & 0xffffffffu);
+        return hipSuccess;
+    }
+    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
+    if (e == hipSuccess)
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, 64 * kSegWWaves, (size_t)lds);
+    if (e != hipSuccess)
+        return e;
+    *wgs = (int64_t)(cus > 0 ? cus : 1) * (per_cu > 0 ? per_cu : 1);
+    if (slot)
+        slot->store((uint64_t)lds << 32 | (uint64_t)*wgs, std::memory_order_release);
+    return hipSuccess;
 }
 
 bool segw_fits(const Shape &sh, int w)
@@ -635,20 +673,17 @@ hipError_t launch_segw(const Shape &sh, int w, const void *ws, const uint16_t *f
     a.div_wps = make_fastdiv(a.wps);
     a.div_khci = make_fastdiv(a.Kh * a.Ci);
     a.div_ci = make_fastdiv(a.Ci);
-    const void *f = op == Op16::BF16 ? segw_fn<BF16Op>(sh, wm, d) : segw_fn<F16Op>(sh, wm, d);
-    int dev = 0, cus = 0, per_cu = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess)
-        e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)d.lds);
-    if (e == hipSuccess)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, 64 * kSegWWaves, (size_t)d.lds);
+    const bool large = d.grans > kSegWSmall;
+    const int al = sh.S * 2 % 8 == 0 ? 0 : sh.S * 2 % 4 == 0 ? 1 : 2;
+    const void *f = op == Op16::BF16 ? segw_fn<BF16Op>(wm, large, al) : segw_fn<F16Op>(wm, large, al);
+    const int id = (((op == Op16::BF16) * kSegWN + wm - 1) * 2 + large) * 3 + al;
+    int64_t wgs;
+    const hipError_t e = segw_resident(f, id, d.lds, &wgs);
     if (e != hipSuccess)
         return e;
     // one resident round of workgroups over the channel groups
     const int64_t gy = (sh.Co + 32 * wm - 1) / (32 * wm), need = ((int64_t)a.nblk + kSegWWaves - 1) / kSegWWaves;
-    int64_t gx = (int64_t)(cus > 0 ? cus : 1) * (per_cu > 0 ? per_cu : 1) / gy;
+    int64_t gx = wgs / gy;
     gx = gx < 1 ? 1 : gx > need ? need : gx;
     void *args[] = {&a};
     return hipLaunchKernel(f, dim3((uint32_t)gx, (uint32_t)gy), dim3(64 * kSegWWaves), args, (size_t)d.lds, st);
