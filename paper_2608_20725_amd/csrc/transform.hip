@@ -12,7 +12,9 @@
 //   * pieces: any other C_i, undilated: a workgroup reads the input rows of
 //             a piece of the window tensor in their own order and puts the
 //             piece together in LDS.
-//   * gather: the rest (dilated layers, very small ones).  A thread assembles
+//   * pieces3: smaller 3-channel layers, undilated and unpadded (16-bit with
+//             K_h <= 3): the gather below with one load per 3-channel pixel.
+//   * gather: the rest (dilated layers, smaller ones).  A thread assembles
 //             one 16-byte granule of the flat window tensor element by
 //             element; granules may straddle strips.
 // All zero the pad bytes that follow the window tensor.
@@ -44,6 +46,7 @@ struct TArgs {
     uint64_t win_elems;
     uint64_t win_bytes, pad_end;
     uint64_t grans;          // gather: 16-byte granules of the window tensor
+    uint64_t in_pixels;      // pieces3: pixels of the input (N * H_i * W_i)
     uint32_t cu;             // pieces: units per pixel
     uint32_t spb, segs, cpb; // pieces: strips per block; pieces per strip, columns per piece
     uint32_t xcd_order;      // vec, pieces: 1 = XCD-aware block order, 0 = linear (ablation)
@@ -315,6 +318,82 @@ __device__ inline void store_elem(uint32_t *w, int e, uint32_t bits)
     }
 }
 
+// The gather of the 3-channel layers with one load per piece: a 16-byte
+// granule of the window tensor (8 fp16 or 4 fp32 elements) spans at most 4
+// (fp16) or 2 (fp32) pieces, a piece being the 3 channels of one input pixel
+// (one column of one filter row of one strip).  Each piece is read with one
+// load, 8 bytes for fp16 (6 used) and 12 for fp32, instead of one load per
+// element; the granule is assembled in registers and stored whole, so a
+// wave's stores stay one contiguous 1 KiB run.  An 8-byte fp16 read would
+// reach 2 bytes past the last pixel of the input: that piece is read as 4 + 2
+// bytes.  For window tensors too small for transform_pieces: against the
+// element gather, us, fp32 7x7 at 74x74, 20 images (8.1 MB), 4.7 and 5.5; fp16
+// 3x3 at 36x41, 51 images (1.2 MB), 3.5 and 4.0.
+template <int ELT>
+__global__ __launch_bounds__(kThreads) void transform_pieces3(TArgs a)
+{
+    constexpr uint32_t V = 16 / ELT;                // elements per granule
+    constexpr int NP = ELT == 2 ? 4 : 2;            // pieces a granule can touch
+    const uint64_t g = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (blockIdx.x == 0)
+        zero_pad(a);
+    if (g >= a.grans)
+        return;
+    // first element of this granule (win_elems < 2^32, checked on the host)
+    const uint32_t e0 = (uint32_t)(g * V);
+    uint32_t q = fdiv(e0, a.div_L);
+    const uint32_t pos = e0 - q * a.L;
+    uint32_t seg = fdiv(pos, a.div_Ci);              // k*K_h + u of the first piece
+    const uint32_t r0 = pos - seg * 3;               // its first channel used
+    const uint32_t segs = a.L / 3;                   // pieces per strip (W_i * K_h)
+    uint32_t el[NP * 3];                             // the pieces' elements (ELT bytes each)
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+        el[3 * j] = el[3 * j + 1] = el[3 * j + 2] = 0u;
+        // piece j holds granule elements 3j - r0 .. 3j - r0 + 2
+        if (3 * j >= (int)(r0 + V) || (uint64_t)e0 + 3 * j - r0 >= a.win_elems)
+            continue;
+        if (seg == segs) {  // into the next strip
+            seg = 0;
+            ++q;
+        }
+        const uint32_t k = fdiv(seg, a.div_Kh), u = seg - k * a.Kh;
+        const uint32_t i = fdiv(q, a.div_Ho), m = q - i * a.Ho;
+        const uint64_t px = ((uint64_t)i * a.Hi + m * a.s + u) * a.Wi + k;  // input pixel
+        const char *src = a.in + px * (3 * ELT);
+        if (ELT == 4) {
+            uint32_t v[3];
+            __builtin_memcpy(v, src, 12);
+            el[3 * j] = v[0]; el[3 * j + 1] = v[1]; el[3 * j + 2] = v[2];
+        } else {
+            uint64_t v;  // one 8-byte load (the last pixel: 4 + 2 bytes)
+            if (px + 1 < a.in_pixels) {
+                __builtin_memcpy(&v, src, 8);
+            } else {
+                uint32_t lo;
+                uint16_t hi;
+                __builtin_memcpy(&lo, src, 4);
+                __builtin_memcpy(&hi, src + 4, 2);
+                v = lo | ((uint64_t)hi << 32);
+            }
+            el[3 * j] = (uint32_t)v & 0xffffu;
+            el[3 * j + 1] = (uint32_t)(v >> 16) & 0xffffu;
+            el[3 * j + 2] = (uint32_t)(v >> 32) & 0xffffu;
+        }
+        ++seg;
+    }
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (uint32_t t = 0; t < V; ++t) {
+        // element t of the granule is element r0 + t of the pieces' run
+        // (r0 < 3)
+        const uint32_t bits = r0 == 0 ? el[t] : r0 == 1 ? el[t + 1] : el[t + 2];
+        store_elem<ELT>(w, (int)t, bits);
+    }
+    // bytes past the window tensor are inside the zero pad: zeros are written
+    *reinterpret_cast<uint4 *>(a.ws + g * 16) = make_uint4(w[0], w[1], w[2], w[3]);
+}
+
 template <int ELT>
 __global__ __launch_bounds__(kThreads) void transform_gather(TArgs a)
 {
@@ -378,6 +457,86 @@ bool transform_range_ok(const Shape &sh)
     return (uint64_t)sh.win_elems + 16 < (1ull << 32);
 }
 
+namespace {
+
+// How transform_pieces divides a layer's window tensor.
+struct PieceGrid {
+    int64_t cpb, spb, segs;  // columns and strips per piece, pieces per strip
+    int64_t blocks;
+    int64_t ub, cu;          // bytes of a unit, units per pixel
+};
+
+PieceGrid piece_grid(const Shape &sh)
+{
+    PieceGrid g;
+    const int64_t colb = sh.Kh * sh.Ci * sh.elt, pxb = sh.Ci * sh.elt;
+    // pieces of at most 16 KiB (eight blocks per CU), smaller ones while there
+    // is less than one per CU (512 or 1024 pieces of one image's split strips
+    // measured up to 1.1 us slower).  Whole strips share a piece only beyond
+    // four pieces per CU: each strip adds K_h rows to what the piece's four
+    // waves read one after another (fp16 padded 3x3 at 110x15, 3 channels, 110
+    // images: 31 strips a piece 20.7 us, 11 strips 11.1, the element gather 4.8).
+    const int64_t most = kPieceBytes / colb, want = 256, shared = 1024;
+    g.cpb = sh.Wi < most ? sh.Wi : most;
+    g.spb = 1;
+    if (g.cpb < sh.Wi || sh.strips < want) {
+        int64_t segs = (sh.Wi + g.cpb - 1) / g.cpb;
+        if (sh.strips * segs < want)
+            segs = (want + sh.strips - 1) / sh.strips;
+        g.cpb = (sh.Wi + segs - 1) / segs;
+        g.cpb = g.cpb < 4 ? (sh.Wi < 4 ? sh.Wi : 4) : g.cpb;
+        g.cpb = g.cpb < most ? g.cpb : most;
+    } else {
+        g.spb = kPieceBytes / (sh.Wi * colb);
+        const int64_t lim = sh.strips / shared;
+        g.spb = g.spb < lim ? g.spb : lim;
+        g.spb = g.spb < 1 ? 1 : g.spb;
+    }
+    g.segs = (sh.Wi + g.cpb - 1) / g.cpb;
+    g.blocks = (sh.strips + g.spb - 1) / g.spb * g.segs;
+    g.ub = pxb % 8 == 0 ? 8 : pxb % 4 == 0 && sh.Ci != 3 ? 4 : sh.elt;
+    g.cu = pxb / g.ub;
+    return g;
+}
+
+// Where transform_pieces is ahead of the gathers, fitted to 4000 layers (GPU
+// time).  What it costs is the rows its waves read one after another: a piece
+// of r rows takes r/4 passes of about half a microsecond, and 2048 pieces are
+// resident at once, so the window tensor has to be large enough for its
+// passes.  Against the gathers (us):
+//   fp32 from 10 MiB, 5 MiB a pass: 3x3 23 channels at 57x62, 11.7 MiB in one
+//   pass, 6.3 and 6.9; 7x7 padded 3 channels at 45x45, 116 images, 16.3 MiB in
+//   seven, 10.3 and 7.9.
+//   16-bit from 512 KiB, 1.5 MiB a pass (2 MiB with 3 channels): 3x3 at
+//   107x107, 7.5 MiB in three, 7.1 and 7.5; 3x3 padded stride 2 at 126x31, 126
+//   images, 4.2 MiB in six, 8.8 and 5.4.  More than 3 channels in one pass
+//   always pay, and so do two passes of up to 512 pieces, which do not wait for
+//   one another (5x5 stride 2 54 channels at 32x32, 1.2 MiB, 3.4 and 3.9; 3
+//   channels at 66x66, 0.6 MiB, 3.4 and 4.0), unless the rows are long runs of
+//   2-byte units (5x5 209 channels at 10x10, 1.7 MiB: 4.7 and 3.8).
+//   One-row filters, which the gather reads in input order, 16-bit from 4 MiB
+//   (6 MiB with 2-byte units) and more than 3 channels: 1x1 stride 2 68
+//   channels, 7.6 MiB, 4.9 and 6.8; 299 channels, 4.0 MiB, 7.2 and 4.8.
+// One and two channels stay with the gather (5x5 one channel, 32 MB: 11.3 vs 8.9).
+bool pieces_pay(const Shape &sh, const PieceGrid &g)
+{
+    constexpr int64_t kMiB = 1 << 20, kResident = 2048;
+    if (sh.Ci <= (sh.Kh > 1 ? 2 : 3))
+        return false;
+    const int64_t per = (g.spb * sh.Kh + 3) / 4, win = sh.win_bytes;
+    const double passes = (double)per * (g.blocks > kResident ? (double)g.blocks / kResident : 1.);
+    if (sh.elt == 4)
+        return win >= 10 * kMiB && win >= 5. * kMiB * passes;
+    if (sh.Kh == 1)
+        return win >= (g.ub == 2 ? 6 : 4) * kMiB;
+    const bool short_rows = g.ub > 2 || g.cpb * g.cu <= 768;
+    if (win >= kMiB / 2 && short_rows && ((per <= 2 && g.blocks <= 512) || (passes == 1. && sh.Ci > 3)))
+        return true;
+    return win >= (sh.Ci == 3 ? 2. : 1.5) * kMiB * passes;
+}
+
+}  // namespace
+
 hipError_t launch_transform(const Shape &sh, const void *in, void *ws, hipStream_t st, const Tuning &t,
                             const Pad *pad)
 {
@@ -430,57 +589,35 @@ hipError_t launch_transform(const Shape &sh, const void *in, void *ws, hipStream
     if (blocks > 0x7fffffffull)
         return hipErrorInvalidValue;
     // pieces: undilated layers whose columns leave room for two in a piece,
-    // where the window tensor is large enough to repay the second pass
-    // through LDS: 16-bit from 512 KiB on (3x5 36 channels, 1.0 MB: 3.5 vs
-    // 4.3 us; 7x7 3-channel, 1.1 MB: even), fp32, with half the elements per
-    // granule, from 4 MiB (7x7 3-channel, 2.1 MB: 4.4 vs 3.8; 3x3 30
-    // channels, 9.3 MB: 5.7 vs 6.1).  One-row filters, whose gather reads in
-    // input order, from 4 MiB and more than 3 channels (1x1 100 channels
-    // fp16, 20 MB: 8.0 vs 15.2; 141 channels fp32, 2.7 MB: 4.9 vs 3.8; 3
-    // channels fp16, 4.8 MB: 7.0 vs 6.2); one and two channels stay with the
-    // gather (5x5 one channel, 32 MB: 11.3 vs 8.9).
-    // IM2WIN_TRANSFORM_KERNEL=pieces takes it wherever it can run, =gather
-    // nowhere.
+    // where it pays (pieces_pay).  IM2WIN_TRANSFORM_KERNEL=pieces takes it
+    // wherever it can run, =gather nowhere.
     const int64_t colb = sh.Kh * sh.Ci * sh.elt;
-    if (sh.d == 1 && 2 * colb <= kPieceBytes && !t.transform_gather &&
-        (t.transform_pieces || (sh.Ci > (sh.Kh > 1 ? 2 : 3) &&
-                                (int64_t)a.grans >= (sh.elt == 4 || sh.Kh == 1 ? 1 << 18 : 1 << 15)))) {
-        // pieces of at most 16 KiB (eight blocks per CU), smaller ones while
-        // there is less than one per CU (512 or 1024 pieces measured up to
-        // 1.1 us slower on single images, even on large batches)
-        const int64_t most = kPieceBytes / colb, want = 256;
-        int64_t cpb = sh.Wi < most ? sh.Wi : most, spb = 1;
-        if (cpb < sh.Wi || sh.strips < want) {
-            int64_t segs = (sh.Wi + cpb - 1) / cpb;
-            if (sh.strips * segs < want)
-                segs = (want + sh.strips - 1) / sh.strips;
-            cpb = (sh.Wi + segs - 1) / segs;
-            cpb = cpb < 4 ? (sh.Wi < 4 ? sh.Wi : 4) : cpb;
-            cpb = cpb < most ? cpb : most;
-        } else {
-            spb = kPieceBytes / (sh.Wi * colb);
-            const int64_t lim = sh.strips / want;
-            spb = spb < lim ? spb : lim;
-            spb = spb < 1 ? 1 : spb;
+    if (sh.d == 1 && 2 * colb <= kPieceBytes && !t.transform_gather) {
+        const PieceGrid pg = piece_grid(sh);
+        if ((t.transform_pieces || pieces_pay(sh, pg)) && pg.blocks <= 0x7fffffff) {
+            a.cpb = (uint32_t)pg.cpb;
+            a.spb = (uint32_t)pg.spb;
+            a.segs = (uint32_t)pg.segs;
+            a.cu = (uint32_t)pg.cu;
+            a.div_cu = make_fastdiv(a.cu);
+            const bool narrow = pg.cpb * pg.cu <= 256;  // one unit per lane, U times, covers a row
+            const void *f =
+                sh.Ci == 3   ? (sh.elt == 4     ? (const void *)&transform_pieces<4, 3>
+                                : pg.cpb <= 128 ? (const void *)&transform_pieces<2, 6, 1>
+                                                : (const void *)&transform_pieces<2, 6, 2>)
+                : pg.ub == 8 ? (narrow ? (const void *)&transform_pieces<8, 1> : (const void *)&transform_pieces<8, 2>)
+                : pg.ub == 4 ? (narrow ? (const void *)&transform_pieces<4, 1> : (const void *)&transform_pieces<4, 4>)
+                             : (narrow ? (const void *)&transform_pieces<2, 1> : (const void *)&transform_pieces<2, 4>);
+            return hipLaunchKernel(f, dim3((uint32_t)pg.blocks), dim3(kThreads), args, 0, st);
         }
-        a.cpb = (uint32_t)cpb;
-        a.spb = (uint32_t)spb;
-        a.segs = (uint32_t)((sh.Wi + cpb - 1) / cpb);
-        const int64_t nb = (sh.strips + spb - 1) / spb * a.segs;
-        const int64_t pxb = sh.Ci * sh.elt;
-        const int ub = pxb % 8 == 0 ? 8 : pxb % 4 == 0 && sh.Ci != 3 ? 4 : (int)sh.elt;
-        a.cu = (uint32_t)(pxb / ub);
-        a.div_cu = make_fastdiv(a.cu);
-        const bool narrow = cpb * a.cu <= 256;  // one unit per lane, U times, covers a row
-        const void *f =
-            sh.Ci == 3 ? (sh.elt == 4  ? (const void *)&transform_pieces<4, 3>
-                          : cpb <= 128 ? (const void *)&transform_pieces<2, 6, 1>
-                                       : (const void *)&transform_pieces<2, 6, 2>)
-            : ub == 8  ? (narrow ? (const void *)&transform_pieces<8, 1> : (const void *)&transform_pieces<8, 2>)
-            : ub == 4  ? (narrow ? (const void *)&transform_pieces<4, 1> : (const void *)&transform_pieces<4, 4>)
-                       : (narrow ? (const void *)&transform_pieces<2, 1> : (const void *)&transform_pieces<2, 4>);
-        if (nb <= 0x7fffffff)
-            return hipLaunchKernel(f, dim3((uint32_t)nb), dim3(kThreads), args, 0, st);
+    }
+    // pieces3: 16-bit only with filters of up to 3 rows (a granule's pixels
+    // otherwise come from up to four input rows: 11x11 even with the gather)
+    if (sh.Ci == 3 && sh.d == 1 && a.ph == 0 && a.pw == 0 && !t.transform_gather && !t.transform_pieces &&
+        (sh.elt == 4 || sh.Kh <= 3)) {
+        a.in_pixels = (uint64_t)sh.N * a.Hi * a.Wi;
+        const void *f = sh.elt == 4 ? (const void *)&transform_pieces3<4> : (const void *)&transform_pieces3<2>;
+        return hipLaunchKernel(f, dim3((uint32_t)blocks), dim3(kThreads), args, 0, st);
     }
     // gather: element indices fit 32 bits (transform_range_ok)
     const void *f = sh.elt == 4 ? (const void *)&transform_gather<4> : (const void *)&transform_gather<2>;

@@ -124,6 +124,18 @@ def test_transform_3ch_pieces_equal_gather(shape, dtype, monkeypatch):
     assert torch.equal(outs[0], outs[1])
 
 
+@pytest.mark.parametrize("dtype", DTYPES, ids=["f32", "f16", "bf16"])
+@pytest.mark.parametrize("shape", [s for s in PIECES3 if s[2] < 100] + [(5, 3, 31, 15, 3, 5, 2), (1, 3, 3, 2, 3, 1, 1)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_transform_3ch_small_default(shape, dtype):
+    """Small 3-channel layers as the default takes them: granules that end in
+    a pixel, a column and a strip, and an input that ends with its last read."""
+    N, Ci, H, W, Kh, Kw, s = shape
+    x, w = workloads.draw(N, Ci, H, W, 2, Kh, Kw, seed=17 + sum(shape))
+    say("transform", shape, dtype)
+    _compare(Run(x, w, s, dtype, conv=False), x)
+
+
 UNALIGNED = [(2, 3, 12, 12, 3, 3, 1), (3, 5, 11, 13, 5, 3, 2), (1, 7, 9, 31, 9, 2, 3), (2, 1, 8, 8, 8, 8, 1),
              (2, 3, 227, 40, 11, 11, 4), (1, 3, 30, 300, 27, 5, 1), (2, 6, 10, 10, 2, 2, 3)]
 

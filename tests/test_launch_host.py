@@ -16,7 +16,7 @@ ROOT = os.path.dirname(HERE)
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 PRELUDE = '''
-import ctypes, sys
+import ctypes, os, sys
 i64 = ctypes.c_int64
 class Call(ctypes.Structure):
     _fields_ = [(n, ctypes.c_longlong) for n in ("kind", "func", "value", "gx", "gy", "block")]
@@ -27,7 +27,17 @@ lib.conv_workspace_bytes.argtypes = [i64] * 8 + [ctypes.c_int]
 fns = {0: lib.conv_im2win_fp32, 1: lib.conv_im2win_fp16, 2: lib.conv_im2win_bf16}
 for f in fns.values():
     f.argtypes = [ctypes.c_void_p, i64, ctypes.c_void_p, ctypes.c_void_p] + [i64] * 8 + [ctypes.c_void_p]
+lib.conv_im2win_transform.argtypes = [ctypes.c_void_p, ctypes.c_void_p] + [i64] * 9 + [ctypes.c_int, ctypes.c_void_p]
 ATTR, LAUNCH, QUERY = 0, 1, 2
+def transform(shape, dt, kernel=None):
+    """The launch of a layer's transform, the kernel forced or the default."""
+    os.environ["IM2WIN_TRANSFORM_KERNEL"] = kernel or ""
+    need = lib.conv_workspace_bytes(*shape, dt)
+    N, Ci, H, W, Co, Kh, Kw, s = shape
+    rc = lib.conv_im2win_transform(1 << 40, 1 << 44, need, N, Ci, H, W, Co, Kh, Kw, s, dt, None)
+    assert rc == 0, rc
+    (c,) = calls()
+    return c
 def conv(shape, dt):
     """The conv call of a layer (buffers that no call touches)."""
     need = lib.conv_workspace_bytes(*shape, dt)
@@ -97,4 +107,39 @@ def test_segment_kernel_repeated_call_asks_the_driver_nothing(shim):
     for c in again:
         assert (c.func, c.value, c.gx, c.gy, c.block) == tuple(getattr(first[-1], n) for n in
                                                                ("func", "value", "gx", "gy", "block"))
+    ''')
+
+
+@pytest.mark.parametrize("shape,dt,want", [
+    # narrow images: a piece of many strips is many short rows for four waves
+    ((125, 3, 90, 13, 16, 7, 7, 2), 1, "gather"), ((73, 3, 68, 9, 16, 5, 5, 1), 2, "gather"),
+    ((67, 3, 57, 14, 16, 7, 7, 1), 2, "gather"), ((108, 3, 35, 35, 16, 5, 5, 1), 1, "gather"),
+    ((113, 3, 98, 15, 16, 7, 7, 2), 0, "3ch"), ((112, 3, 108, 39, 16, 3, 3, 2), 0, "3ch"),
+    # small 3-channel tensors: one load per pixel
+    ((1, 3, 32, 32, 16, 3, 3, 1), 0, "3ch"), ((112, 3, 27, 27, 16, 3, 3, 1), 1, "3ch"),
+    # long runs of 2-byte units
+    ((1, 299, 65, 65, 16, 1, 1, 1), 1, "gather"), ((16, 209, 10, 10, 16, 5, 5, 1), 1, "gather"),
+    # where pieces are ahead: the stems, inner layers off 8 channels, small ones of one row pass
+    ((128, 3, 227, 227, 96, 11, 11, 4), 1, "pieces"), ((32, 3, 230, 230, 64, 7, 7, 2), 0, "pieces"),
+    ((128, 3, 224, 224, 64, 3, 3, 1), 1, "pieces"), ((128, 3, 224, 224, 64, 3, 3, 1), 0, "pieces"),
+    ((92, 52, 81, 81, 51, 3, 3, 1), 1, "pieces"), ((7, 36, 31, 45, 100, 3, 5, 2), 1, "pieces"),
+    ((128, 100, 28, 28, 100, 1, 1, 1), 1, "pieces"),
+])
+def test_transform_kernel_by_its_row_passes(shim, shape, dt, want):
+    """The default transform of unaligned channel counts: the element gather,
+    the one-load-per-pixel gather of 3 channels, or pieces put together in LDS."""
+    run(shim, '''
+    shape, dt, want = %r, %r, %r
+    got = transform(shape, dt).func
+    forced = {k: transform(shape, dt, k).func for k in ("pieces", "gather")}
+    kind = next((k for k, f in forced.items() if f == got), "3ch")
+    assert kind == want, kind
+    ''' % (shape, dt, want))
+
+
+def test_transform_pieces_grid(shim):
+    """Strips share a piece only beyond four pieces per CU."""
+    run(shim, '''
+    for shape, dt in (((110, 3, 110, 15, 16, 3, 3, 1), 1), ((300, 5, 40, 9, 16, 3, 3, 1), 0)):
+        assert transform(shape, dt, "pieces").gx >= 1024
     ''')
