@@ -536,25 +536,38 @@ int dma32_default(const Shape &sh)
     // per CU: 7x7 C=64 stride 2 at 224x224, 95.0 vs 92.7 TFLOP/s in the
     // benchmark step (3x3 C=64 -> 128 stride 1 at 112x112: 94.8 vs 97.7)
     const bool strided = sh.s > 1 && sh.Kw > sh.s;
-    const char *name;
+    const char *name = nullptr;
     if (!aligned) {
-        // Unaligned windows (C_i % 4 != 0, the 3-channel stems): the tile
-        // whose busiest CU has the least work, ceil(tiles / 256) tiles of
-        // px x ch sums.  The 6-pixel lane tile is ahead of the 8-pixel one
-        // (7x7 C_i=3 stride 2 67.2 vs 64.1 TFLOP/s, 3x3 C_i=3 36.6 vs 34.4)
-        // and, at even balance, of the 4-pixel one (7x7 stride 2 3 -> 64 at
-        // 224x224, 32 images, 13 * 128 against 9 * 192 pixels: 121.5 vs 126.4
-        // us).  The 32 x 32 tile whose waves split the taps does its sums
-        // 1.25 times slower (same layer, 4 images: 30.4 vs 26.7), but fills
-        // the chip: one image 28.9 -> 13.1, 11x11 3 -> 96 stride 4 54.9 ->
-        // 13.0, 3x3 217 -> 63 at 28x28, 4 images, 268 -> 41.  A tile alone on
-        // its CU leaves its loads uncovered (3x3 50 -> 100 at 28x28, 170
-        // tiles of 128 pixels 52 us, 1352 of 32 x 32 30).
-        const int64_t n6 = tiles(192, 64), n4 = tiles(128, 64), ns = tiles(32, 32);
-        const int64_t c6 = (n6 + 255) / 256 * 192 * 64 * (n6 <= 256 ? 125 : 100);
-        const int64_t c4 = (n4 + 255) / 256 * 128 * 64 * (n4 <= 256 ? 125 : 100);
-        const int64_t cs = (ns + 255) / 256 * 32 * 32 * 125;
-        name = cs < c4 && cs < c6 ? "p4c4l8s2k16g4t4" : c4 < c6 ? "p4c8l8s2k16g4" : "p6c8l8s2k16g4";
+        // Unaligned windows (C_i % 4 != 0, the 3-channel stems): the tile with
+        // the least time in nanoseconds for n tiles on 256 CUs and k taps
+        // (whole 16-tap stages), fitted to 2300 layers: what a round of tiles
+        // costs by itself and per tap, and what the first stages' uncovered
+        // loads cost per tap.  The 32 x 32 tile whose waves split the taps
+        // fills the chip with few pixels (7x7 3 -> 64 stride 2, one image 28.9
+        // -> 13.1 us; 3x3 217 -> 63 at 28x28, 4 images, 268 -> 41) but pays
+        // 0.8 us a round for its first loads and the sum over the waves, which
+        // short windows do not repay (3x3 3 -> 3 at 79x79, 99 images: 68.1
+        // against 38.2 with 192-pixel tiles).  Of the others the 6-pixel lane
+        // tile has the cheaper sums, the 4-pixel one the finer grid (7x7 stride
+        // 2 3 -> 64 at 224x224, 32 images, 13 * 128 against 9 * 192 pixels: 121.5
+        // vs 126.4 us); the 8-pixel one is behind both (7x7 stride 2 64.1
+        // against 67.2 TFLOP/s).
+        const struct {
+            const char *name;
+            int64_t px, ch;
+            double round, tap, first;
+        } cand[] = {{"p6c8l8s2k16g4", 192, 64, 2470., 45., 110.},
+                    {"p4c8l8s2k16g4", 128, 64, 1530., 31., 80.},
+                    {"p4c4l8s2k16g4t4", 32, 32, 816., 4.8, 11.}};
+        double least = -1.;
+        for (const auto &c : cand) {
+            const double rounds = (double)((tiles(c.px, c.ch) + 255) / 256), k = (double)sh.K_pad32;
+            const double cost = rounds * (c.round + c.tap * k) + c.first * k;
+            if (least < 0. || cost < least) {
+                least = cost;
+                name = c.name;
+            }
+        }
     } else if (tiles256 <= 128 && sh.s > 1 && sh.Kw > 2 * sh.s) {
         name = "p8c8l8s2k16t4";  // few tiles of wide strided windows: the choice the plan tests fix
     } else if (tiles(32, 32) <= 512) {

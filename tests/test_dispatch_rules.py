@@ -1,0 +1,40 @@
+"""Kernel choice where the tile that suits most layers is behind: layers on
+which a default once ran slower than the kernel it had replaced, each with the
+kernel measured ahead (GPU time of the conv call, us, in the comments).  No
+call here reaches a GPU."""
+import os
+
+import pytest
+
+import paper_2608_20725_amd as pkg
+
+
+@pytest.fixture(autouse=True)
+def clean_env(monkeypatch):
+    for v in [k for k in os.environ if k.startswith("IM2WIN_")]:
+        monkeypatch.delenv(v)
+    if not os.path.exists(pkg.library_path()):
+        from paper_2608_20725_amd import build
+        build.build()
+
+
+def name(shape, dt, **kw):   # N, Ci, H, W, Co, Kh, Kw, s
+    return pkg.conv_im2win_kernel_name(*shape, dt, **kw)
+
+
+@pytest.mark.parametrize("shape,want", [
+    # short windows: the tap-split tile's rounds cost more than its taps
+    ((99, 3, 79, 79, 3, 3, 3, 1), "p4c8l8s2k16g4"),       # 68.1 tap-split, 38.2 with 192-pixel tiles
+    ((71, 1, 115, 115, 10, 2, 2, 2), "p4c8l8s2k16g4"),    # 31.3, 17.3
+    ((39, 17, 111, 111, 11, 1, 1, 1), "p4c8l8s2k16g4"),   # 59.8, 35.5
+    ((125, 3, 111, 18, 3, 3, 1, 1), "p4c8l8s2k16g4"),     # 30.9, 15.7
+    ((48, 3, 95, 95, 3, 2, 1, 2), "p4c8l8s2k16g4"),       # 17.4, 11.3
+    # few tiles or longer windows: the tap-split tile
+    ((1, 3, 230, 230, 64, 7, 7, 2), "p4c4l8s2k16g4t4"), ((4, 217, 28, 28, 63, 3, 3, 1), "p4c4l8s2k16g4t4"),
+    ((1, 15, 37, 33, 223, 1, 1, 1), "p4c4l8s2k16g4t4"),
+    # large grids
+    ((32, 3, 230, 230, 64, 7, 7, 2), "p4c8l8s2k16g4"), ((128, 3, 227, 227, 64, 7, 7, 2), "p4c8l8s2k16g4"),
+    ((128, 3, 227, 227, 96, 11, 11, 4), "p4c12l8s2k16g4"),
+])
+def test_dma32_unaligned(shape, want):
+    assert name(shape, "f32") == "conv_fp32_dma " + want
