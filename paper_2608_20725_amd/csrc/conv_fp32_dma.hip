@@ -580,8 +580,10 @@ int dma32_default(const Shape &sh)
         name = sh.K >= 128 ? "p4c4l8s2k16t8w8" : "p4c4l8s2k16t4";
     } else if (tiles(64, 64) <= 256) {
         // 3x3 C=256 at 14x14, 16 images, 109 -> 61 us; 3x3 C=512 at 7x7, 32
-        // images, 204 -> 114 (p4c8l8s2k16t4w8: 66 and 123)
-        name = "p8c8l8s2k16t8w8";
+        // images, 204 -> 114 (p4c8l8s2k16t4w8: 66 and 123).  Windows shorter
+        // than a 128-tap stage: the small four-wave form again (3x3 stride 2 4
+        // -> 43, 13328 pixels: 11.3 us, p8c8l8s2k16t4 9.9, p4c4l8s2k16t4 8.1)
+        name = sh.K >= 128 ? "p8c8l8s2k16t8w8" : "p4c4l8s2k16t4";
     } else if (tiles256 <= 1024) {
         // (at most 128 tiles: 3x3 C=512 at 7x7, 128 images, 212 -> 205 us
         // against p8c8l8s2k16t4; 3x3 C=256 at 14x14, 32 images, 114 -> 106)

@@ -38,3 +38,13 @@ def name(shape, dt, **kw):   # N, Ci, H, W, Co, Kh, Kw, s
 ])
 def test_dma32_unaligned(shape, want):
     assert name(shape, "f32") == "conv_fp32_dma " + want
+
+
+@pytest.mark.parametrize("shape,want", [
+    # windows shorter than a 128-tap stage
+    ((17, 4, 57, 57, 43, 3, 3, 2), "p4c4l8s2k16t4"),      # 11.3 with p8c8l8s2k16t8w8, 9.9 p8c8l8s2k16t4, 8.1
+    ((8, 8, 12, 38, 176, 1, 1, 1), "p4c4l8s2k16t4"), ((6, 8, 35, 35, 192, 7, 1, 2), "p4c4l8s2k16t4"),
+    ((16, 256, 16, 16, 256, 3, 3, 1), "p8c8l8s2k16t8w8"),
+])
+def test_dma32_aligned_short_windows(shape, want):
+    assert name(shape, "f32") == "conv_fp32_dma " + want
