@@ -568,14 +568,14 @@ int dma32_default(const Shape &sh)
                 name = c.name;
             }
         }
-    } else if (tiles256 <= 128 && sh.s > 1 && sh.Kw > 2 * sh.s) {
-        name = "p8c8l8s2k16t4";  // few tiles of wide strided windows: the choice the plan tests fix
     } else if (tiles(32, 32) <= 512) {
         // Small grids: a 32 x 32 tile's sums take a quarter of the time of
         // the 64 x 64 tile's four waves (conv call, us, against
         // p8c8l8s2k16t4): 3x3 C=256 at 14x14, 1 / 8 images 101 -> 27.5, 104
         // -> 37.9; 3x3 C=512 at 7x7 196 -> 53; 3x3 C=64 at 56x56 30.5 ->
-        // 11.2; 1x1 C=1024 51 -> 19.  Windows shorter than its 128-tap stage
+        // 11.2; 1x1 C=1024 51 -> 19; wide strided windows gain most: 7x7 stride
+        // 2 C=192 -> 11, 8 pixels, 381 -> 75; 11x11 stride 4 C=192 -> 15, 2508
+        // pixels, 943 -> 179).  Windows shorter than its 128-tap stage
         // take the four-wave form (1x1 32 -> 48: 6.7 against 8.3).
         name = sh.K >= 128 ? "p4c4l8s2k16t8w8" : "p4c4l8s2k16t4";
     } else if (tiles(64, 64) <= 256) {

@@ -48,3 +48,13 @@ def test_dma32_unaligned(shape, want):
 ])
 def test_dma32_aligned_short_windows(shape, want):
     assert name(shape, "f32") == "conv_fp32_dma " + want
+
+
+@pytest.mark.parametrize("shape,want", [
+    # wide strided windows on few tiles, like any other few-tile layer
+    ((2, 64, 28, 28, 64, 7, 7, 2), "p4c4l8s2k16t8w8"), ((1, 192, 19, 19, 11, 7, 7, 2), "p4c4l8s2k16t8w8"),
+    ((8, 32, 60, 60, 15, 11, 11, 4), "p4c4l8s2k16t8w8"), ((24, 16, 33, 33, 40, 5, 5, 2), "p4c4l8s2k16t8w8"),
+    ((2, 64, 28, 28, 64, 7, 7, 1), "p4c4l8s2k16t8w8"),
+])
+def test_dma32_wide_strided_windows(shape, want):
+    assert name(shape, "f32") == "conv_fp32_dma " + want
