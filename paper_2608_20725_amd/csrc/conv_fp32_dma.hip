@@ -599,7 +599,11 @@ int dma32_default(const Shape &sh)
     const int64_t pad64 = (sh.Co + 63) / 64 * 64 - sh.Co, pad96 = (sh.Co + 95) / 96 * 96 - sh.Co;
     if (pad96 < pad64 && ((sh.P + 127) / 128) * ((sh.Co + 95) / 96) >= 1024)
         name = aligned ? "p4c12l8s2k16" : "p4c12l8s2k16g4";
-    const int pick = dma32_find(name);
+    // a filter too long for 128-tap stages (their last one ends further past
+    // K_pad32) may still fit 64-tap ones
+    int pick = dma32_find(name);
+    if (!dma32_fits(sh, pick) && aligned)
+        pick = dma32_find(tiles256 <= 128 ? "p8c8l8s2k16t4" : "p4c8l8s2k16t4w8");
     return dma32_fits(sh, pick) ? pick : -1;
 }
 

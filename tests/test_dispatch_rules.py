@@ -58,3 +58,14 @@ def test_dma32_aligned_short_windows(shape, want):
 ])
 def test_dma32_wide_strided_windows(shape, want):
     assert name(shape, "f32") == "conv_fp32_dma " + want
+
+
+def test_dma32_filter_range():
+    """Filter offsets up to one stage past the window need 31 bits: a filter
+    too long for 128-tap stages runs 64-tap ones, and the register-staged
+    kernel only past those."""
+    def at(Ci):
+        return name((1, Ci, 2, 2, 16384, 1, 1, 1), "f32")
+    assert at(32624) == "conv_fp32_dma p4c4l8s2k16t8w8"
+    assert at(32688) == "conv_fp32_dma p4c8l8s2k16t4w8"
+    assert at(32720).startswith("conv_fp32_kernel ")
