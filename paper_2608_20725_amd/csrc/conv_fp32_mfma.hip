@@ -387,29 +387,38 @@ struct MVariant {
     const char *name;
     const void *f;
     int bm, bn, nt;
+    int weight;  // time of a sum beside the 128 x 128 tile's, percent
+    int few;     // tiles up to which a CU's loads stay uncovered, and what that costs, percent
+    int alone;
 };
 
 template <int WM, int WN, int WGM, int WGN, int NS, int KS = 1>
-MVariant m_variant(const char *name)
+MVariant m_variant(const char *name, int weight, int few = 256, int alone = 106)
 {
     using C = MCfg<WM, WN, WGM, WGN, NS, KS>;
-    return MVariant{name, (const void *)&conv_fp32_mfma<C>, C::BM, C::BN, C::NT};
+    return MVariant{name, (const void *)&conv_fp32_mfma<C>, C::BM, C::BN, C::NT, weight, few, alone};
 }
 
 const MVariant *m_variants(int *n)
 {
-    // channels x pixels per workgroup, ring slots
+    // channels x pixels per workgroup, ring slots.  Weights: 3x3 64 -> 128 at
+    // 112x112 (6050 tiles of 128 x 128: 1826 us; 64-row tiles 1880, 32 x 128
+    // 1977, 32 x 256 2031), the tap-split ones against those at even balance.
+    // One workgroup per CU leaves its barriers and load waits uncovered (1x1 140
+    // -> 313 at 18x18, 15 images: 190 tiles 17.7 us, 380 half as large 16.2),
+    // and the two-slot tap-split tile wants more than two (392 tiles 36.3
+    // against 33.2 with four slots, 1520 14.7 against 15.9).
     static const MVariant v[] = {
-        m_variant<2, 2, 2, 2, 2>("c128p128s2"),
-        m_variant<2, 2, 1, 4, 2>("c64p256s2"),
-        m_variant<1, 2, 1, 4, 2>("c32p256s2"),
+        m_variant<2, 2, 2, 2, 2>("c128p128s2", 100),
+        m_variant<2, 2, 1, 4, 2>("c64p256s2", 103),
+        m_variant<1, 2, 1, 4, 2>("c32p256s2", 111),
         // smaller tiles for layers with few output pixels
-        m_variant<1, 2, 2, 2, 2>("c64p128s2"),
-        m_variant<1, 1, 1, 4, 2>("c32p128s2"),
+        m_variant<1, 2, 2, 2, 2>("c64p128s2", 103),
+        m_variant<1, 1, 1, 4, 2>("c32p128s2", 108),
         // the taps of a stage split over four waves (small grids)
-        m_variant<1, 1, 1, 1, 4, 4>("c32p32s4t4"),
-        m_variant<1, 1, 1, 1, 2, 4>("c32p32s2t4"),
-        m_variant<2, 1, 1, 1, 4, 4>("c64p32s4t4"),
+        m_variant<1, 1, 1, 1, 4, 4>("c32p32s4t4", 116),
+        m_variant<1, 1, 1, 1, 2, 4>("c32p32s2t4", 114, 512, 112),
+        m_variant<2, 1, 1, 1, 4, 4>("c64p32s4t4", 111),
     };
     *n = (int)(sizeof v / sizeof v[0]);
     return v;
@@ -454,28 +463,20 @@ int mfma32_default(const Shape &sh)
     const MVariant *v = m_variants(&n);
     // The matrix cores bound these tiles, and a CU's workgroups share them:
     // the time is that of the CU with the most tiles, ceil(tiles / 256) tiles
-    // of bm x bn sums, times what the tile's operand reads cost beside a
-    // 128 x 128 one's (3x3 64 -> 128 at 112x112, 6050 tiles: 1826 us; 64-row
-    // tiles 1880, 32 x 128 1977, 32 x 256 2031).  Against the largest tile
-    // with two workgroups per CU: 3x3 C=512 at 14x14 (576 / 2304 tiles) 848 ->
-    // 713 us, 3x3 C=256 at 14x14 226 -> 207, 1x1 C=1024 at 14x14 457 -> 437.
-    // The tiles whose waves split the taps fill the chip with the fewest
-    // pixels and come within 11 to 16 % of the large ones at even balance (3x3
-    // C=256 at 14x14, one image 55.6 -> 24.9, 128 images 207 -> 191; 3x3 C=512
-    // at 7x7, 128 images, 170 -> 157; 5x5 40 -> 88 at 42x42, 3 images, 28.4
-    // -> 17.5).
-    static const int weight[] = {100, 103, 111, 103, 108, 116, 114, 111};  // by variant
+    // of bm x bn sums, times what the tile's operand reads cost beside a 128 x
+    // 128 one's.  Against the largest tile with two workgroups per CU: 3x3
+    // C=512 at 14x14 (576 / 2304 tiles) 848 -> 713 us, 3x3 C=256 at 14x14 226
+    // -> 207, 1x1 C=1024 at 14x14 457 -> 437.  The tiles whose waves split the
+    // taps fill the chip with the fewest pixels and come within 11 to 16 % of
+    // the large ones at even balance (3x3 C=256 at 14x14, one image 55.6 ->
+    // 24.9, 128 images 207 -> 191; 3x3 C=512 at 7x7, 128 images, 170 -> 157;
+    // 5x5 40 -> 88 at 42x42, 3 images, 28.4 -> 17.5).
     int best = 0;
     int64_t least = -1;
     for (int i = 0; i < n; ++i) {
         const int64_t tiles = ((sh.P + v[i].bn - 1) / v[i].bn) * ((sh.Co + v[i].bm - 1) / v[i].bm);
-        // one workgroup per CU leaves its barriers and load waits uncovered
-        // (1x1 140 -> 313 at 18x18, 15 images: 190 tiles 17.7 us, 380 half as
-        // large 16.2)
-        // (and the two-slot tap-split tile wants more than two per CU: 392
-        // tiles 36.3 against 33.2 with four slots, 1520 14.7 against 15.9)
-        const int64_t alone = i == 6 && tiles <= 512 ? 112 : tiles <= 256 ? 106 : 100;
-        const int64_t cost = (tiles + 255) / 256 * v[i].bm * v[i].bn * weight[i] * alone;
+        const int64_t alone = tiles <= v[i].few ? v[i].alone : 100;
+        const int64_t cost = (tiles + 255) / 256 * v[i].bm * v[i].bn * v[i].weight * alone;
         if (least < 0 || cost < least) {
             best = i;
             least = cost;
