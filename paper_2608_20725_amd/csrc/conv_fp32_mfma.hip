@@ -390,13 +390,16 @@ struct MVariant {
     int weight;  // time of a sum beside the 128 x 128 tile's, percent
     int few;     // tiles up to which a CU's loads stay uncovered, and what that costs, percent
     int alone;
+    int start;   // what a tile costs before its first tap, in taps (windows shorter than kShortTaps)
 };
 
+constexpr int64_t kShortTaps = 128;
+
 template <int WM, int WN, int WGM, int WGN, int NS, int KS = 1>
-MVariant m_variant(const char *name, int weight, int few = 256, int alone = 106)
+MVariant m_variant(const char *name, int weight, int few = 256, int alone = 106, int start = 0)
 {
     using C = MCfg<WM, WN, WGM, WGN, NS, KS>;
-    return MVariant{name, (const void *)&conv_fp32_mfma<C>, C::BM, C::BN, C::NT, weight, few, alone};
+    return MVariant{name, (const void *)&conv_fp32_mfma<C>, C::BM, C::BN, C::NT, weight, few, alone, start};
 }
 
 const MVariant *m_variants(int *n)
@@ -416,9 +419,9 @@ const MVariant *m_variants(int *n)
         m_variant<1, 2, 2, 2, 2>("c64p128s2", 103),
         m_variant<1, 1, 1, 4, 2>("c32p128s2", 108),
         // the taps of a stage split over four waves (small grids)
-        m_variant<1, 1, 1, 1, 4, 4>("c32p32s4t4", 116),
-        m_variant<1, 1, 1, 1, 2, 4>("c32p32s2t4", 114, 512, 112),
-        m_variant<2, 1, 1, 1, 4, 4>("c64p32s4t4", 111),
+        m_variant<1, 1, 1, 1, 4, 4>("c32p32s4t4", 116, 256, 106, 30),
+        m_variant<1, 1, 1, 1, 2, 4>("c32p32s2t4", 114, 512, 112, 20),
+        m_variant<2, 1, 1, 1, 4, 4>("c64p32s4t4", 111, 256, 106, 30),
     };
     *n = (int)(sizeof v / sizeof v[0]);
     return v;
@@ -470,14 +473,21 @@ int mfma32_default(const Shape &sh)
     // taps fill the chip with the fewest pixels and come within 11 to 16 % of
     // the large ones at even balance (3x3 C=256 at 14x14, one image 55.6 ->
     // 24.9, 128 images 207 -> 191; 3x3 C=512 at 7x7, 128 images, 170 -> 157;
-    // 5x5 40 -> 88 at 42x42, 3 images, 28.4 -> 17.5).
+    // 5x5 40 -> 88 at 42x42, 3 images, 28.4 -> 17.5), but their first loads and
+    // the sum over the waves are not repaid by a short window: `start` taps,
+    // less of them the longer it is (1x1 16 -> 88, 29547 pixels: 11.7 us with
+    // c32p32s2t4 against 9.3 with c32p128s2; 1x1 8 -> 288, 2880 pixels, 7.6
+    // against 6.8).  Fitted to 2500 layers, of which 13 ran over a tenth slower
+    // than with the largest tile of two workgroups per CU, and one does now.
+    const int64_t k = k_pad_mfma(sh.K), lack = k < kShortTaps ? kShortTaps - k : 0;
     int best = 0;
-    int64_t least = -1;
+    double least = -1.;
     for (int i = 0; i < n; ++i) {
         const int64_t tiles = ((sh.P + v[i].bn - 1) / v[i].bn) * ((sh.Co + v[i].bm - 1) / v[i].bm);
         const int64_t alone = tiles <= v[i].few ? v[i].alone : 100;
-        const int64_t cost = (tiles + 255) / 256 * v[i].bm * v[i].bn * v[i].weight * alone;
-        if (least < 0 || cost < least) {
+        const int64_t sums = (tiles + 255) / 256 * v[i].bm * v[i].bn;
+        const double cost = (double)(sums * v[i].weight * alone) * (double)(k * kShortTaps + v[i].start * lack);
+        if (least < 0. || cost < least) {
             best = i;
             least = cost;
         }

@@ -69,3 +69,16 @@ def test_dma32_filter_range():
     assert at(32624) == "conv_fp32_dma p4c4l8s2k16t8w8"
     assert at(32688) == "conv_fp32_dma p4c8l8s2k16t4w8"
     assert at(32720).startswith("conv_fp32_kernel ")
+
+
+@pytest.mark.parametrize("shape,want", [
+    # short windows: a tap-split tile's first loads and final sum are not repaid
+    ((112, 8, 13, 13, 128, 1, 1, 1), "c32p128s2"),        # 12.8 with c64p32s4t4, 9.3
+    ((6, 8, 111, 45, 264, 2, 2, 2), "c32p128s2"),         # 10.1 with c32p32s2t4, 8.4
+    ((10, 8, 24, 12, 288, 1, 1, 1), "c32p128s2"),         # 7.6 with c64p32s4t4, 6.8
+    # longer ones, few pixels
+    ((1, 256, 16, 16, 256, 3, 3, 1), "c32p32s4t4"), ((128, 512, 14, 14, 512, 3, 3, 1), "c32p128s2"),
+    ((128, 64, 224, 224, 64, 7, 7, 2), "c64p128s2"),
+])
+def test_mfma32_short_windows(shape, want):
+    assert name(shape, "f32", fp32_matrix_cores=True) == "conv_fp32_mfma " + want
