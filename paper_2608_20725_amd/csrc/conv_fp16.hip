@@ -900,9 +900,6 @@ int pipe_default(const Shape &sh)
     // bytes per clock and CU), so tiles are as large as the grid allows.
     auto tiles = [&](int64_t bm, int64_t bn) { return ((sh.P + bn - 1) / bn) * ((sh.Co + bm - 1) / bm); };
     const int64_t t128 = tiles128(sh), t256 = tiles(256, 128);
-    // C_o that fills 64-channel rows much better than 128-channel ones (144:
-    // 192 against 256; 7x7 64 -> 144 dilated 47.4 vs 34.5)
-    const bool half = round_up(sh.Co, 128) * 4 > round_up(sh.Co, 64) * 5;
     // 256 x 128 over eight waves, three slots, one workgroup per CU: a
     // quarter fewer bytes per FLOP than 128 x 128, but nothing runs beside its
     // first loads and its stores, so only for windows of 32 stages and more
@@ -920,7 +917,7 @@ int pipe_default(const Shape &sh)
             return pipe_find("c256p128s3w8");
         return pipe_find("c128p128s1");
     }
-    if (sh.Co <= 64 || half)
+    if (sh.Co <= 64)
         return pipe_find("c64p128s3");
     // At most one workgroup per CU: a deeper ring instead of a second
     // workgroup covers the loads, in the largest tile that spreads over the
@@ -928,13 +925,26 @@ int pipe_default(const Shape &sh)
     // 3x3 C=512 at 7x7, 24 images, 24.1 vs 31.2; c128p64s4 same layer, 128
     // images, 30.4 vs 32.0; c128p128s3w8 3x3 C=512 at 14x14, 32 images, 38.0
     // vs 46.3, 5x5 96 -> 256 at 24x24, 32 images, 26.0 vs 32.0, 1x1 512 ->
-    // 2048 at 7x7, 32 images, 14.0 vs 15.2.
-    if (t128 <= 64)
+    // 2048 at 7x7, 32 images, 14.0 vs 15.2.  By the tiles' own number, since
+    // C_o pads each differently: 7x7 536 -> 136, 3696 pixels, 95.6 with c64p64s4
+    // (174 tiles) and 158.2 with c64p128s3; 11x11 stride 4 32 -> 288, 5915
+    // pixels, 28.1 with c64p128s3 (235 tiles) and 32.8 with c128p128s3w8.
+    if (tiles(64, 64) <= 256)
         return pipe_find("c64p64s4");
-    if (t128 <= 128)
+    if (tiles(128, 64) <= 256)
         return pipe_find("c128p64s4");
+    if (tiles(64, 128) <= 256)
+        return pipe_find("c64p128s3");
     if (t128 <= 256)
         return pipe_find("c128p128s3w8");
+    // C_o that fills 64-channel rows much better than 128-channel ones (144:
+    // 192 against 256; 7x7 64 -> 144 dilated 47.4 vs 34.5), while the busiest
+    // CU has less work for it: a 64 x 128 tile takes 0.7 of a 128 x 128 one
+    // (3x3 to 11x11, C_o 129 to 192, 128 x 128 against 64 x 128 tiles: 257 to
+    // 330 tiles 1.12 to 1.21, 331 to 512 0.85 to 0.96, 513 to 700 1.09 to 1.25)
+    auto rounds = [](int64_t n) { return (n + 255) / 256; };
+    if (round_up(sh.Co, 128) * 4 > round_up(sh.Co, 64) * 5 && rounds(tiles(64, 128)) * 7 < rounds(t128) * 10)
+        return pipe_find("c64p128s3");
     // up to two 128 x 128 tiles per CU, unevenly spread: one 256 x 128 tile
     // each instead (3x3 C=256 dilated at 28x28, 32 images, 392 / 196 tiles,
     // 42.6 vs 40.2; 3x3 C=512 at 14x14, 64 images, 67.4 vs 56.9)
