@@ -364,7 +364,7 @@ int direct_default(const Shape &sh)
     if (aligned && sh.Kw == 3 && sh.d == 1 && sh.Co > 64 && sh.Co <= 128 && sh.K <= 576)
         return -1;
     int n, best = -1;
-    int64_t best_cost = 0;
+    int64_t best_cost = 0, best_rounds = 0;
     const DirVariant *v = dir_variants(&n);
     for (int t = 0; t < n; ++t) {
         if (!direct_fits(sh, t))
@@ -377,6 +377,7 @@ int direct_default(const Shape &sh)
         if (best < 0 || cost < best_cost) {
             best = t;
             best_cost = cost;
+            best_rounds = rounds;
         }
     }
     if (best < 0)
@@ -384,8 +385,13 @@ int direct_default(const Shape &sh)
     // With long windows the row kernel's 64 x 64 tile with four slots is
     // ahead where this one would use as large a tile (3x3 C=512 at 7x7, 24
     // images: 24.1 vs 29.3 us; 3x3 C=256 at 14x14, 12 images: 14.8 vs 16.4;
-    // 1x1 1024 -> 256 at 14x14, 16 images: 10.3 vs 9.8).
+    // 1x1 1024 -> 256 at 14x14, 16 images: 10.3 vs 9.8), and with longer ones
+    // where two rounds of this one's would run (7x7 stride 2 208 -> 344, 1458
+    // pixels: 40.0 vs 59.6 us; over 24 layers even at 2000 taps, 0.92 of the
+    // time at 3000, 0.81 at 6000, 0.68 from 8192 on).
     if (aligned && sh.K >= 1536 && v[best].bm == 64 && v[best].bn == 64)
+        return -1;
+    if (aligned && sh.K >= 2560 && best_rounds > 1)
         return -1;
     // the largest tile the layer's channels allow decides whether the grid is small
     const int64_t big = sh.Co % 4 == 0 ? 64 : 32;

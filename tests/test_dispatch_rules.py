@@ -96,3 +96,14 @@ def test_mfma32_short_windows(shape, want):
 def test_row_tiles_by_their_grid(shape, want, monkeypatch):
     monkeypatch.setenv("IM2WIN_FP16_KERNEL", "pipe")
     assert name(shape, "f16") == "conv_fp16_pipe " + want
+
+
+@pytest.mark.parametrize("shape,want", [
+    # long windows on two rounds of small-grid tiles
+    ((18, 208, 24, 24, 344, 7, 7, 2), "conv_fp16_pipe c64p64s4"),     # 59.6 small-grid, 40.0
+    ((4, 544, 72, 70, 96, 7, 7, 2), "conv_fp16_pipe c64p64s4"),       # 139.4, 85.8
+    # one round, or shorter windows
+    ((1, 256, 16, 16, 256, 3, 3, 1), "conv_fp16_direct c32p16w8"), ((8, 512, 9, 9, 512, 3, 3, 1), "conv_fp16_direct c32p32w8"),
+])
+def test_direct_long_windows(shape, want):
+    assert name(shape, "f16") == want
