@@ -593,8 +593,12 @@ int col_default(const Shape &sh)
     // the one-slot row kernel is faster on many-tile layers with C_o >= 128,
     // except 3x3 layers with C_o <= 128 (3x3 64 -> 128 at 112x112: column
     // kernel 664 vs 636 TFLOP/s) or stride 1 (3x3 C=256 at 28x28: 124 vs 134
-    // us; with stride 2 at 56x56 past 150 vs 139)
-    if (fp16_single_slot_rows(sh) && !(sh.Kw == 3 && (sh.Co <= 128 || sh.s == 1)))
+    // us; with stride 2 at 56x56 past 150 vs 139) whose columns K_h*C_i fill
+    // their slices of T_pad taps: with half of them zeros it is behind (3x3 8 ->
+    // 240 at 87x87, 39 images, 46.1 vs 40.0; over 150 layers of 1.4 to 1.6 times
+    // the row kernel's taps 1.10, of up to 1.35 times 0.98)
+    const bool filled = sh.Kw * sh.Tp * 5 <= sh.K_pad * 7;
+    if (fp16_single_slot_rows(sh) && !(sh.Kw == 3 && (sh.Co <= 128 || (sh.s == 1 && filled))))
         return -1;
     // C_o <= 64: 64 x 128 tiles, three workgroups per CU, more bytes in
     // flight for these HBM-bound layers (3x3 C=64 at 56x56: 484 vs 431

@@ -107,3 +107,14 @@ def test_row_tiles_by_their_grid(shape, want, monkeypatch):
 ])
 def test_direct_long_windows(shape, want):
     assert name(shape, "f16") == want
+
+
+@pytest.mark.parametrize("shape,want", [
+    # column slices half full of zeros (K_h*C_i of T_pad taps), many tiles
+    ((43, 16, 106, 108, 200, 1, 3, 1), "conv_fp16_pipe c128p128s1"),  # 67.3 column-staged, 48.5
+    ((39, 8, 87, 87, 240, 3, 3, 1), "conv_fp16_pipe c128p128s1"),     # 46.1, 40.0
+    ((128, 64, 58, 58, 256, 3, 3, 1), "conv_fp16_col k3c128p128t32s2"),
+    ((128, 256, 28, 28, 256, 3, 3, 1), "conv_fp16_col k3c128p128t32s2"),
+])
+def test_column_kernel_needs_filled_slices(shape, want):
+    assert name(shape, "f16") == want
