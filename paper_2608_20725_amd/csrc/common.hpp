@@ -475,12 +475,14 @@ hipError_t launch_conv_fp16_col(const Shape &sh, int v, const Tuning &t, const v
                                 uint16_t *out, hipStream_t st, Op16 op);
 // Row-per-pixel fp16 tiles: default for the layer and name; 128 x 128 tiles
 // of the layer; whether bm-row channel tiles suit its C_o; the workspace
-// bytes kept for fp32 partial tiles.
+// bytes kept for fp32 partial tiles; the K split a default plan makes of a
+// variant (1: none).
 int pipe_default(const Shape &sh);
 const char *pipe_name(int v);
 int64_t tiles128(const Shape &sh);
 bool rows_fit(const Shape &sh, int64_t bm);
 int64_t split_reserve_bytes(const Shape &sh);
+int pipe_split_default(const Shape &sh, int v);
 // Output tiles of a row-per-pixel variant on a layer, and its 64-tap stages.
 int64_t pipe_tiles(const Shape &sh, int v);
 int64_t pipe_tile_elems(int v);

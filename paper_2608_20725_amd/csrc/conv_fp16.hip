@@ -853,32 +853,49 @@ int64_t pipe_tile_elems(int v)
     return (int64_t)pv.bm * pv.bn;
 }
 
-// Bytes conv_workspace_bytes reserves after the packed filter for fp32
-// partial tiles: ks 128 x 128 tiles per output tile of a layer with at most
+// The K ranges conv_workspace_bytes leaves room for after the packed filter:
+// ks fp32 partial tiles of 128 x 128 per output tile of a layer with at most
 // 128 of them and at least 32 stages, for the largest ks <= 4 that keeps the
-// workspace within the layer's im2col matrix.  Plans no longer split K by
-// default (the deeper rings below fill such grids without partial sums: 3x3
-// C=512 at 14x14, 16 images, split two ways 39.9 us, c128p64s4 29.2), but
-// the size is part of the interface, and a forced split uses the room.
-int64_t split_reserve_bytes(const Shape &sh)
+// workspace within the layer's im2col matrix (1: no room).  The size is part
+// of the interface; forced splits and the default one below use the room.
+int split_reserve_ways(const Shape &sh)
 {
     const int v = pipe_find("c128p128s2");
     const int64_t tiles = pipe_tiles(sh, v), nst = sh.K_pad / BK;
     if (sh.Ci % 8 != 0 || sh.Co < 128 || tiles > 128 || nst < 32)
-        return 0;
+        return 1;
     // layers that ran a column-staged kernel have no such region
     if (sh.Kw == 3 && sh.Co <= 256 && col_fits(sh, col_find(sh.Co == 128 ? "k3c128p128t32s2" : "k3c64p128t32s2")))
-        return 0;
+        return 1;
     if (sh.Kw == 7 && sh.Co == 128 && col_fits(sh, col_find("k7c64p256t16s3")))
-        return 0;
+        return 1;
     const int64_t base = sh.pad_end + sh.Co_pad * sh.Kw * sh.Tp * 2;  // window tensor, pad, packed filter
     const int64_t im2col = sh.P * sh.K * 2;
     for (int ks = 4; ks >= 2; --ks) {
         const int64_t spl = (nst + ks - 1) / ks, bytes = ks * tiles * pipe_tile_elems(v) * 4;
         if ((ks - 1) * spl < nst && base + bytes <= im2col)
-            return bytes;
+            return ks;
     }
-    return 0;
+    return 1;
+}
+
+int64_t split_reserve_bytes(const Shape &sh)
+{
+    const int ks = split_reserve_ways(sh), v = pipe_find("c128p128s2");
+    return ks > 1 ? ks * pipe_tiles(sh, v) * pipe_tile_elems(v) * 4 : 0;
+}
+
+// The K split a default plan makes of row-per-pixel variant v (1: none), in
+// 128 x 128 tiles.  Four ranges of very long windows, where the grid would
+// run four-slot 128 x 64 tiles: the second kernel's pass over the partial
+// tiles is then repaid (conv call, us, four ranges against c128p64s4: 5x5
+// stride 2 624 -> 208, 5865 pixels, 72.1 and 83.1; 7x7 272 -> 360, 2850
+// pixels, 61.6 and 70.6; over 20 layers of 10240 taps and more 0.87 to 0.98).
+// Shorter ones do not repay it (5000 to 10000 taps 0.92 to 1.08, 3500 1.25),
+// nor do two or three ranges (1.0 to 1.4).
+int pipe_split_default(const Shape &sh, int v)
+{
+    return v == pipe_find("c128p64s4") && sh.K >= 10240 && split_reserve_ways(sh) == 4 ? 4 : 1;
 }
 
 // Whether channel tiles of bm rows pad C_o by at most a fifth or so (the

@@ -152,14 +152,20 @@ bool split_ok(const Shape &sh, int ks)
     return ks >= 1 && ks <= kMaxSplit && (ks - 1) * spl < nst;
 }
 
-// The K split of a row-per-pixel plan: none unless the tuning forces one.
+// The K split of a row-per-pixel plan: forced by the tuning, else the default
+// for the layer unless a tile is forced.
 int with_split(const Shape &sh, const Tuning &t, Plan16 *p)
 {
     p->ks = 1;
     if (p->fam != Fam16::Pipe) {
         return t.fp16_split > 1 ? IM2WIN_EINVAL : IM2WIN_OK;
     }
-    const int ks = t.fp16_split > 0 ? t.fp16_split : 1;
+    int ks = t.fp16_split > 0 ? t.fp16_split : 1;
+    if (t.fp16_split == 0 && t.fp16_tile < 0) {
+        ks = pipe_split_default(sh, p->v);
+        if (ks > 1)
+            p->v = pipe_find("c128p128s2");
+    }
     if (!split_ok(sh, ks))
         return IM2WIN_EINVAL;
     p->ks = ks;

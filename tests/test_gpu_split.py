@@ -10,7 +10,8 @@ import torch
 
 import oracle
 import paper_2608_20725_amd as pkg
-from gpu_util import TOL, check_full, oracle_inputs, rel_err, say
+from gpu_util import Run, TOL, check_full, check_sampled, oracle_inputs, rel_err, say
+from paper_2608_20725_amd import workloads
 
 pytestmark = pytest.mark.gpu
 
@@ -107,3 +108,22 @@ def test_split_needs_its_workspace(monkeypatch):
     with pytest.raises(pkg.Im2winError) as e:
         run_split(x, w, 1, torch.float16, 2, monkeypatch, extra=False)
     assert e.value.status == EWORKSPACE
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16], ids=["f16", "bf16"])
+def test_default_split(dtype):
+    """The split a plan makes by default (windows of 10240 taps and more):
+    sampled outputs against the oracle, the same bits twice, and nothing past
+    the workspace that conv_workspace_bytes names."""
+    shape = (3, 272, 37, 36, 360, 7, 7, 1)
+    assert pkg.conv_im2win_kernel_name(*shape, dtype) == "conv_fp16_pipe c128p128s2 k4"
+    N, Ci, H, W, Co, Kh, Kw, s = shape
+    say("default split", shape, dtype)
+    x, w = workloads.draw(N, Ci, H, W, Co, Kh, Kw, seed=71)
+    r = Run(x, w, s, dtype)
+    check_sampled(r, x, w, seed=5, max_mac=1e9)
+    r.check_workspace_guard()
+    r.check_out_guards()
+    first = r.out.clone()
+    r.rerun_conv()
+    assert torch.equal(first.view(torch.int16), r.out.view(torch.int16))

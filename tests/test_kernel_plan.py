@@ -198,15 +198,36 @@ def test_split_reported_and_refused_where_it_cannot_run(monkeypatch):
     assert name(sh, "f32").startswith("conv_fp32_dma ")
 
 
-@pytest.mark.parametrize("layer", workloads.ALL, ids=lambda l: l.name)
-def test_default_plan_workspace_not_above_im2col_by_the_split(layer):
-    # a K split the planner makes by default keeps the whole 16-bit workspace
-    # within the layer's im2col matrix
-    sh = lay(layer)
-    n = name(sh, "f16")
-    if n.split()[-1].startswith("k") and n.split()[0] == "conv_fp16_pipe":
-        ws = pkg.conv_workspace_bytes(*sh, "f16")
-        assert ws <= pkg.conv_im2col_bytes(sh[0], sh[1], sh[2], sh[3], sh[5], sh[6], sh[7], "f16")
+SPLIT = [(5, 624, 72, 72, 208, 5, 5, 2), (3, 272, 37, 36, 360, 7, 7, 1), (4, 512, 31, 31, 512, 7, 7, 1)]
+
+
+@pytest.mark.parametrize("sh", [lay(l) for l in workloads.ALL] + SPLIT, ids=lambda s: "x".join(map(str, s)))
+def test_default_plan_workspace_not_above_im2col_by_the_split(sh):
+    # where room is kept for a K split's partial tiles (the sizes below), the
+    # whole 16-bit workspace stays within the layer's im2col matrix, and a
+    # split that the planner makes by default has that room
+    N, Ci, H, W, Co, Kh, Kw, s = sh
+    Ho, Wo = (H - Kh) // s + 1, (W - Kw) // s + 1
+    up = lambda a, b: (a + b - 1) // b * b
+    base = up(N * Ho * W * Kh * Ci * 2, 256) + 256 + up(Co, 256) * Kw * up(Kh * Ci, 64) * 2
+    ws, n = pkg.conv_workspace_bytes(*sh, "f16"), name(sh, "f16")
+    split = n.split()[0] == "conv_fp16_pipe" and n.split()[-1].startswith("k") and int(n.split()[-1][1:])
+    if ws > base:
+        assert ws <= pkg.conv_im2col_bytes(N, Ci, H, W, Kh, Kw, s, "f16")
+    assert split == (4 if sh in SPLIT else False), n
+    if split:
+        assert ws - base == split * up(N * Ho * Wo, 128) * up(Co, 128) * 4
+
+
+def test_default_split_of_very_long_windows(monkeypatch):
+    sh = SPLIT[0]    # 15600 taps: 83.1 us with c128p64s4, 72.1 in four ranges
+    assert name(sh, "f16") == name(sh, "bf16") == "conv_fp16_pipe c128p128s2 k4"
+    assert name((5, 312, 72, 72, 208, 5, 5, 2), "f16") == "conv_fp16_pipe c128p64s4"    # 7800
+    monkeypatch.setenv("IM2WIN_FP16_SPLIT", "1")
+    assert name(sh, "f16") == "conv_fp16_pipe c128p64s4"
+    monkeypatch.delenv("IM2WIN_FP16_SPLIT")
+    monkeypatch.setenv("IM2WIN_FP16_TILE", "c128p128s2")
+    assert name(sh, "f16") == "conv_fp16_pipe c128p128s2"
 
 
 @pytest.mark.parametrize("shape,want", [
