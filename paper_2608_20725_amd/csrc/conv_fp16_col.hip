@@ -588,8 +588,9 @@ int col_default(const Shape &sh)
     const char *name = nullptr;
     // grids of at most one 128 x 128 tile per CU run the row kernel's deeper
     // rings (3x3 C=128 at 28x28, 32 images: 17.0 vs 15.9 us; 3x3 C=256 at
-    // 14x14, 64 images: 26.4 vs 24.8), short 3x3 windows (K <= 576) excepted
-    const bool small = sh.Co > 64 && tiles128(sh) <= 256 && !(sh.Kw == 3 && sh.Co <= 128 && sh.K <= 576);
+    // 14x14, 64 images: 26.4 vs 24.8; up to 64 input and 128 output
+    // channels 0.71 to 0.96 of the column kernel's time)
+    const bool small = sh.Co > 64 && tiles128(sh) <= 256;
     // the one-slot row kernel is faster on many-tile layers with C_o >= 128,
     // except 3x3 layers with C_o <= 128 (3x3 64 -> 128 at 112x112: column
     // kernel 664 vs 636 TFLOP/s) or stride 1 (3x3 C=256 at 28x28: 124 vs 134

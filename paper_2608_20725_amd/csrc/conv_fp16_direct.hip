@@ -351,17 +351,14 @@ bool direct_fits(const Shape &sh, int pick)
 //   3x3 217 -> 256 62 vs 58).  Windows of at most two steps (K <= 64) stay with
 //   the kernels that hold a short window in registers or LDS: there are no
 //   taps to split.
-// 3x3 layers of up to 64 input and 65 to 128 output channels stay with the
-// column-staged kernel: its 128 x 128 tile is even with this one from about
-// 8000 pixels on (C_o = 96, 8748 pixels: 11.7 vs 10.6), and the plan of the
-// smaller ones is fixed by the plan tests although this kernel is ahead there.
+// 3x3 layers of up to 64 input and 65 to 128 output channels gain as much: 0.32
+// to 0.43 of the column-staged kernel's time up to 4000 pixels, 0.53 at 8000
+// (3x3 64 -> 104 at 32x32, 2 images, 11.0 -> 4.3 us).
 int direct_default(const Shape &sh)
 {
     constexpr int64_t kCUs = 256;
     const bool aligned = sh.Ci % 8 == 0;
     if (!aligned && sh.K <= 64)
-        return -1;
-    if (aligned && sh.Kw == 3 && sh.d == 1 && sh.Co > 64 && sh.Co <= 128 && sh.K <= 576)
         return -1;
     int n, best = -1;
     int64_t best_cost = 0, best_rounds = 0;

@@ -118,3 +118,13 @@ def test_direct_long_windows(shape, want):
 ])
 def test_column_kernel_needs_filled_slices(shape, want):
     assert name(shape, "f16") == want
+
+
+@pytest.mark.parametrize("shape,want", [
+    # 3x3, up to 64 input and 65 to 128 output channels: by the grid, as any other layer
+    ((1, 64, 16, 16, 128, 3, 3, 1), "conv_fp16_direct c32p16w8"), ((2, 64, 24, 24, 128, 3, 3, 1), "conv_fp16_direct c32p16w8"),
+    ((5, 64, 30, 30, 128, 3, 3, 1), "conv_fp16_direct c64p32w8"), ((20, 64, 24, 24, 128, 3, 3, 1), "conv_fp16_pipe c128p64s4"),
+    ((60, 64, 24, 24, 128, 3, 3, 1), "conv_fp16_pipe c128p128s3w8"), ((80, 64, 24, 24, 128, 3, 3, 1), "conv_fp16_col k3c128p128t32s2"),
+])
+def test_few_channels_by_grid(shape, want):
+    assert name(shape, "f16") == want
