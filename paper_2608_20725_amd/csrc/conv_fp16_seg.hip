@@ -772,8 +772,18 @@ int seg_default(const Shape &sh)
                 least = cost;
             }
         }
-        if (best >= 0)
-            return best;
+        // Strips of at most 12 pixels (3/8 of a block) lose to the tiled and
+        // register-staged kernels once windows are long and every wave has
+        // many such blocks (32-channel pieces of them): 3x3 73 -> 536 with 10
+        // pixels a strip, 11550 in all, 54.8 us against 29.1; 7x7 13 -> 344
+        // with 9, 9954, 35.2 against 24.9.  With 300 to 500 taps and with
+        // fewer blocks it is ahead as often as behind.
+        if (best >= 0) {
+            const int wm = kSegW[best - n].wm;
+            const int64_t pieces = nblk * ((sh.Co + 32 * wm - 1) / (32 * wm)) * wm;
+            if (sh.Wo > 12 || sh.K < 500 || pieces < 12288)
+                return best;
+        }
     }
     // C_o <= 64: 64 x 128 tiles with a 16 KiB segment area when the
     // segments fit it (five workgroups per CU instead of two: 7x7 s2 C_i=3

@@ -131,3 +131,16 @@ def test_column_kernel_needs_filled_slices(shape, want):
 ])
 def test_few_channels_by_grid(shape, want):
     assert name(shape, "f16") == want
+
+
+@pytest.mark.parametrize("shape,want", [
+    # strips of few pixels, long windows, many blocks a wave: a block's other lanes are idle
+    ((27, 71, 26, 11, 672, 3, 3, 1), "conv_fp16_kernel c128p128u"),   # 42.2 one-wave, 26.8
+    ((14, 13, 85, 15, 344, 7, 7, 1), "conv_fp16_kernel c128p128u"),   # 35.2, 24.9
+    ((71, 73, 12, 12, 733, 3, 3, 1), "conv_fp16_kernel c128p128u"),   # 57.2, 40.9
+    # few blocks, shorter windows, longer strips
+    ((40, 71, 26, 11, 256, 3, 3, 1), "conv_fp16_seg w32"), ((27, 31, 26, 11, 672, 3, 3, 1), "conv_fp16_seg w96"),
+    ((27, 71, 26, 18, 672, 3, 3, 1), "conv_fp16_seg w32"), ((128, 3, 227, 227, 96, 11, 11, 4), "conv_fp16_seg w96"),
+])
+def test_segment_waves_on_short_strips(shape, want):
+    assert name(shape, "f16") == want
