@@ -970,8 +970,16 @@ int pipe_default(const Shape &sh)
     // 256 x 256 over eight waves when its grid fills 128 to 256 CUs (cfg4
     // 616 vs 575 TFLOP/s, S4 670 vs 646; with fewer tiles it starves the
     // chip, with more the second round runs partly empty)
-    if (tiles(256, 256) >= 128 && tiles(256, 256) <= 256 && sh.Co >= 256)
-        return pipe_find("c256p256s2w8");
+    if (tiles(256, 256) >= 128 && tiles(256, 256) <= 256 && sh.Co >= 256) {
+        if (rows_fit(sh, 256))
+            return pipe_find("c256p256s2w8");
+        // C_o that it would pad by a third and more: 128-row tiles, with one
+        // slot beyond two of them per CU (0.71 of its time to 512 tiles, 0.83 to
+        // 768, where two slots take 0.92; 3x3 120 -> 520, 11067 pixels, 36.4 us
+        // with it, 30.2 with the column-staged tile that had run there)
+        if (t128 > 512)
+            return pipe_find("c128p128s1");
+    }
     return pipe_find("c128p128s2");
 }
 

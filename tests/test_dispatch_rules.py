@@ -144,3 +144,12 @@ def test_few_channels_by_grid(shape, want):
 ])
 def test_segment_waves_on_short_strips(shape, want):
     assert name(shape, "f16") == want
+
+
+@pytest.mark.parametrize("shape,want", [
+    # 256-row tiles only where C_o fills them
+    ((31, 120, 53, 9, 520, 3, 3, 1), "c128p128s2"), ((23, 96, 19, 63, 289, 3, 3, 1), "c128p128s1"),
+    ((128, 96, 24, 24, 256, 5, 5, 1), "c256p256s2w8"),
+])
+def test_wide_row_tiles_need_filled_rows(shape, want):
+    assert name(shape, "f16") == "conv_fp16_pipe " + want
