@@ -385,13 +385,14 @@ int direct_default(const Shape &sh)
     // 1x1 1024 -> 256 at 14x14, 16 images: 10.3 vs 9.8), and with longer ones
     // where two rounds of this one's would run (7x7 stride 2 208 -> 344, 1458
     // pixels: 40.0 vs 59.6 us; over 24 layers even at 2000 taps, 0.92 of the
-    // time at 3000, 0.81 at 6000, 0.68 from 8192 on).  Where another kernel
+    // time at 3000, 0.81 at 6000, 0.68 from 8192 on; not two of its smallest
+    // tile, 7x7 stride 2 112 -> 224, 1156 pixels, 20.5 vs 24.7).  Where another kernel
     // would run instead, up to 64 channels and on the column-staged one's
     // layers, this one stays ahead (3x3 400 -> 4, 10830 pixels: 16.2 vs 29.9;
     // 7x7 136 -> 72, 4800 pixels, 32.2 vs 47.2).
     if (aligned && sh.K >= 1536 && v[best].bm == 64 && v[best].bn == 64)
         return -1;
-    if (aligned && sh.K >= 2560 && best_rounds > 1 && sh.Co > 64 && col_default(sh) < 0)
+    if (aligned && sh.K >= 2560 && best_rounds > 1 && v[best].bn > 16 && sh.Co > 64 && col_default(sh) < 0)
         return -1;
     // the largest tile the layer's channels allow decides whether the grid is small
     const int64_t big = sh.Co % 4 == 0 ? 64 : 32;

@@ -541,8 +541,8 @@ int dma32_default(const Shape &sh)
         // Unaligned windows (C_i % 4 != 0, the 3-channel stems): the tile with
         // the least time in nanoseconds for n tiles on 256 CUs and k taps
         // (whole 16-tap stages), fitted to 2300 layers: what a round of tiles
-        // costs by itself and per tap, and what the first stages' uncovered
-        // loads cost per tap.  The 32 x 32 tile whose waves split the taps
+        // costs by itself and per tap, and what the first one's uncovered loads
+        // add, in all and per tap.  The 32 x 32 tile whose waves split the taps
         // fills the chip with few pixels (7x7 3 -> 64 stride 2, one image 28.9
         // -> 13.1 us; 3x3 217 -> 63 at 28x28, 4 images, 268 -> 41) but pays
         // 0.8 us a round for its first loads and the sum over the waves, which
@@ -555,14 +555,14 @@ int dma32_default(const Shape &sh)
         const struct {
             const char *name;
             int64_t px, ch;
-            double round, tap, first;
-        } cand[] = {{"p6c8l8s2k16g4", 192, 64, 2470., 45., 110.},
-                    {"p4c8l8s2k16g4", 128, 64, 1530., 31., 80.},
-                    {"p4c4l8s2k16g4t4", 32, 32, 816., 4.8, 11.}};
+            double round, tap, start, first;
+        } cand[] = {{"p6c8l8s2k16g4", 192, 64, 1760., 45., 2000., 110.},
+                    {"p4c8l8s2k16g4", 128, 64, 1100., 31., 1000., 80.},
+                    {"p4c4l8s2k16g4t4", 32, 32, 816., 4.8, 0., 11.}};
         double least = -1.;
         for (const auto &c : cand) {
             const double rounds = (double)((tiles(c.px, c.ch) + 255) / 256), k = (double)sh.K_pad32;
-            const double cost = rounds * (c.round + c.tap * k) + c.first * k;
+            const double cost = rounds * (c.round + c.tap * k) + c.start + c.first * k;
             if (least < 0. || cost < least) {
                 least = cost;
                 name = c.name;

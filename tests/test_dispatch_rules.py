@@ -32,6 +32,8 @@ def name(shape, dt, **kw):   # N, Ci, H, W, Co, Kh, Kw, s
     # few tiles or longer windows: the tap-split tile
     ((1, 3, 230, 230, 64, 7, 7, 2), "p4c4l8s2k16g4t4"), ((4, 217, 28, 28, 63, 3, 3, 1), "p4c4l8s2k16g4t4"),
     ((1, 15, 37, 33, 223, 1, 1, 1), "p4c4l8s2k16g4t4"),
+    ((2, 1, 55, 55, 509, 1, 1, 2), "p4c4l8s2k16g4t4"),    # 10.0 with p4c8l8s2k16g4, 8.6
+    ((126, 1, 9, 9, 125, 3, 3, 1), "p4c4l8s2k16g4t4"),    # 10.0, 8.8
     # large grids
     ((32, 3, 230, 230, 64, 7, 7, 2), "p4c8l8s2k16g4"), ((128, 3, 227, 227, 64, 7, 7, 2), "p4c8l8s2k16g4"),
     ((128, 3, 227, 227, 96, 11, 11, 4), "p4c12l8s2k16g4"),
@@ -102,6 +104,8 @@ def test_row_tiles_by_their_grid(shape, want, monkeypatch):
     # long windows on two rounds of small-grid tiles
     ((18, 208, 24, 24, 344, 7, 7, 2), "conv_fp16_pipe c64p64s4"),     # 59.6 small-grid, 40.0
     ((4, 544, 72, 70, 96, 7, 7, 2), "conv_fp16_pipe c64p64s4"),       # 139.4, 85.8
+    # two rounds of the smallest tile
+    ((4, 112, 39, 39, 224, 7, 7, 2), "conv_fp16_direct c32p16w8"),    # 24.7 with c64p64s4, 20.5
     # where other kernels than that row tile would run
     ((5, 400, 21, 116, 4, 3, 3, 1), "conv_fp16_direct c32p32w8"),     # 29.9 column-staged, 16.2
     ((48, 136, 16, 16, 72, 7, 7, 1), "conv_fp16_direct c32p32w8"),    # 47.2 column-staged, 32.2
