@@ -119,7 +119,12 @@ def _dtype_code(dtype) -> int:
     try:
         return _codes[dtype]
     except (KeyError, TypeError):
-        raise ValueError("dtype must be fp32, fp16 or bf16, got %r" % (dtype,)) from None
+        pass
+    # not a key itself: whatever compares equal to one
+    for known, code in _codes.items():
+        if dtype == known:
+            return code
+    raise ValueError("dtype must be fp32, fp16 or bf16, got %r" % (dtype,))
 
 
 _raw_stream = None

@@ -276,3 +276,26 @@ def test_dilated_rejects(lib):
                                              0, None) == EINVAL
     assert lib.conv_im2win_transform_dilated(v(0x1008), v(0x100000), 1 << 20, 1, 3, 8, 8, 4, 3, 3, 1, 1, 1, 2,
                                              0, None) == EALIGN
+
+
+def test_dtype_codes():
+    """A type by its code, name or torch dtype, or anything equal to one of
+    them, hashable or not; anything else is a ValueError."""
+    import numpy as np
+    import torch
+
+    class Named:   # equal to a name, not hashable
+        __hash__ = None
+
+        def __eq__(self, other):
+            return other == "f16"
+
+    sh = (1, 8, 6, 6, 8, 3, 3, 1)
+    for code, names in ((pkg.F32, ("f32", "fp32", torch.float32, np.int64(0), torch.tensor(0))),
+                        (pkg.F16, ("f16", "fp16", torch.float16, torch.tensor(1), np.array(1), Named())),
+                        (pkg.BF16, ("bf16", torch.bfloat16, 2.0, np.str_("bf16")))):
+        for n in names:
+            assert pkg.conv_workspace_bytes(*sh, n) == pkg.conv_workspace_bytes(*sh, code), n
+    for bad in (3, "f64", None, torch.int32, [], {}):
+        with pytest.raises(ValueError):
+            pkg.conv_workspace_bytes(*sh, bad)
