@@ -17,9 +17,11 @@ from paper_2608_20725_amd import workloads
 pytestmark = pytest.mark.gpu
 
 DTYPES = [torch.float32, torch.float16, torch.bfloat16]
+# small layers as the defaults take them (the small-grid kernels); the other
+# families are forced one by one below
 SHAPES = [
-    (5, 16, 12, 12, 24, 3, 3, 1),     # row-per-pixel fp16 kernel
-    (4, 64, 24, 24, 64, 3, 3, 1),     # column-staged fp16 kernel
+    (5, 16, 12, 12, 24, 3, 3, 1),
+    (4, 64, 24, 24, 64, 3, 3, 1),
     (3, 3, 20, 20, 16, 5, 5, 2),      # 3-channel stem: gather transform, unaligned windows
 ]
 # (n_chunk, with a second stream)
@@ -61,6 +63,48 @@ def test_chunked_equals_full_batch(shape, dtype):
             got = out.cpu()
             bits = torch.int32 if dtype == torch.float32 else torch.int16
             assert torch.equal(got.view(bits), ref.view(bits)), (n_chunk, two)
+
+
+# One layer per kernel family, forced where the default would be another: the
+# filter packed on one stream and read by convs on both, or (direct, one-wave
+# segment, small short-window kernels) the caller's filter read on both.
+FAMILIES = [
+    ("conv_fp16_pipe c64p64s4", "IM2WIN_FP16_TILE", (5, 16, 12, 12, 72, 3, 3, 1), torch.float16),
+    ("conv_fp16_pipe c128p128s3w8", "IM2WIN_FP16_TILE", (5, 64, 14, 14, 130, 3, 3, 1), torch.bfloat16),
+    ("conv_fp16_col k3c64p128t32s2", "IM2WIN_FP16_COL", (4, 64, 24, 24, 64, 3, 3, 1), torch.float16),
+    ("conv_fp16_seg s64p128g1024", "IM2WIN_FP16_SEG", (3, 3, 40, 40, 40, 5, 5, 2), torch.float16),
+    ("conv_fp16_seg w64", "IM2WIN_FP16_SEG", (5, 3, 40, 40, 72, 7, 7, 2), torch.float16),
+    ("conv_fp16_seg w96", "IM2WIN_FP16_SEG", (4, 12, 19, 41, 100, 3, 5, 1), torch.bfloat16),
+    ("conv_fp16_stem m2k2", None, (4, 3, 40, 40, 64, 3, 3, 1), torch.float16),
+    ("conv_fp16_kernel c64p256u", "IM2WIN_FP16_KERNEL=regs", (3, 21, 12, 12, 40, 3, 3, 1), torch.float16),
+    ("conv_fp16_direct c32p16w8", None, (5, 16, 12, 12, 24, 3, 3, 1), torch.bfloat16),
+    ("conv_fp32_stem k27c8", None, (5, 3, 21, 20, 16, 3, 3, 1), torch.float32),
+    ("conv_fp32_stem k27", "IM2WIN_FP32_KERNEL=stem", (3, 3, 40, 40, 16, 3, 3, 1), torch.float32),
+    ("conv_fp32_dma p4c4l8s2k16t8w8", None, (5, 32, 12, 12, 24, 3, 3, 1), torch.float32),
+    ("conv_fp32_dma p4c4l8s2k16g4t4", None, (5, 5, 20, 20, 40, 5, 5, 2), torch.float32),
+]
+
+
+@pytest.mark.parametrize("case", FAMILIES, ids=lambda c: c[0].replace(" ", "-") + "-" + str(c[3])[6:])
+def test_chunked_kernel_families(case, monkeypatch):
+    kernel, var, shape, dtype = case
+    N, Ci, H, W, Co, Kh, Kw, s = shape
+    if var:
+        k, _, v = var.partition("=")
+        monkeypatch.setenv(k, v or kernel.split()[1])
+    for n in (N, 2, 1):
+        got = pkg.conv_im2win_kernel_name(n, Ci, H, W, Co, Kh, Kw, s, dtype)
+        assert got == kernel, (n, got)
+    x, w = workloads.draw(N, Ci, H, W, Co, Kh, Kw, seed=37)
+    full = Run(x, w, s, dtype)
+    check_full(full, x, w)
+    bits = torch.int32 if dtype == torch.float32 else torch.int16
+    aux = torch.cuda.Stream()
+    for n_chunk, two in ((2, True), (1, True), (2, False)):
+        say("chunked", kernel, shape, n_chunk, two)
+        for _ in range(2):
+            out = _run_chunked(x, w, s, dtype, n_chunk, two, aux if two else None)
+            assert torch.equal(out.view(bits), full.out.view(bits)), (n_chunk, two)
 
 
 def check_out(out, x, w, s, dtype):

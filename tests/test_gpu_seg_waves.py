@@ -74,3 +74,41 @@ def test_seg_waves_refused_where_lds_ends():
             pkg.conv_im2win_kernel_name(1, 217, 9, 9, 128, 3, 3, 1, "f16")
     finally:
         del os.environ["IM2WIN_FP16_SEG"]
+
+
+def test_seg_waves_two_threads(monkeypatch):
+    """Two host threads, each with its stream and a layer of its own LDS size
+    on one kernel instance, in turn: every call launches and gives the bits of
+    a single-threaded one."""
+    import threading
+    monkeypatch.setenv("IM2WIN_FP16_SEG", "w32")
+    dt = torch.float16
+    jobs = []
+    for k, shape in enumerate([(3, 3, 40, 41, 40, 7, 5, 1), (3, 3, 40, 41, 40, 7, 7, 1)]):
+        x, w = workloads.draw(*shape[:7], 43 + k)
+        assert pkg.conv_im2win_kernel_name(*shape, dt) == "conv_fp16_seg w32"
+        jobs.append((shape, Run(x, w, shape[7], dt), torch.cuda.Stream()))
+    refs = [r.out.clone() for _, r, _ in jobs]
+    errors = []
+
+    def loop(k):
+        (N, Ci, H, W, Co, Kh, Kw, s), r, st = jobs[k]
+        try:
+            for _ in range(200):
+                pkg.conv_im2win_fp16(r.ws, r.wd, r.out, N, Ci, H, W, s, stream=st)
+            st.synchronize()
+        except Exception as e:
+            errors.append(e)
+
+    for _, r, _ in jobs:
+        r.out.fill_(float("nan"))
+    torch.cuda.synchronize()
+    ts = [threading.Thread(target=loop, args=(k,)) for k in range(2)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    torch.cuda.synchronize()
+    assert not errors, errors
+    for (_, r, _), ref in zip(jobs, refs):
+        assert torch.equal(r.out.view(torch.int16), ref.view(torch.int16))

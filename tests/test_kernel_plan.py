@@ -14,7 +14,7 @@ EINVAL = -1
 VARS = ("IM2WIN_FP16_KERNEL", "IM2WIN_FP16_COL", "IM2WIN_FP16_TILE", "IM2WIN_FP16_SEG", "IM2WIN_FP32_KERNEL",
         "IM2WIN_FP32_TILE", "IM2WIN_FP32_MFMA_TILE", "IM2WIN_TRANSFORM_ORDER", "IM2WIN_TILE_ORDER",
         "IM2WIN_TAP_ORDER", "IM2WIN_FP16_SPLIT", "IM2WIN_FP32_COLS", "IM2WIN_TRANSFORM_KERNEL",
-        "IM2WIN_FP16_PERSIST")
+        "IM2WIN_FP16_PERSIST", "IM2WIN_FP16_DIRECT")
 
 
 @pytest.fixture(autouse=True)
@@ -72,6 +72,11 @@ def test_unknown_tuning_value_refused(monkeypatch, var, value):
     {"IM2WIN_FP16_COL": "k3c64p128t32s2", "IM2WIN_FP16_SEG": "s64p256"},
     {"IM2WIN_FP16_TILE": "c64p128s3", "IM2WIN_FP16_KERNEL": "regs"},
     {"IM2WIN_FP32_KERNEL": "p8c8l8s2k16", "IM2WIN_FP32_TILE": "m4n16f"},
+    {"IM2WIN_FP16_DIRECT": "c32p16w8", "IM2WIN_FP16_COL": "k3c64p128t32s2"},
+    {"IM2WIN_FP16_DIRECT": "c32p16w8", "IM2WIN_FP16_TILE": "c64p128s3"},
+    {"IM2WIN_FP16_DIRECT": "c32p16w8", "IM2WIN_FP16_SEG": "w32"},
+    {"IM2WIN_FP16_DIRECT": "c32p16w8", "IM2WIN_FP16_KERNEL": "regs"},
+    {"IM2WIN_FP16_DIRECT": "c32p16w8", "IM2WIN_FP16_KERNEL": "stem"},
 ], ids=lambda e: "+".join(e))
 def test_contradictory_tuning_refused(monkeypatch, env):
     for k, v in env.items():
@@ -93,6 +98,9 @@ def test_contradictory_tuning_refused(monkeypatch, env):
     ({"IM2WIN_FP16_TILE": "c64p128s3"}, (1, 3, 10, 10, 64, 3, 3, 1), "f16"),
     # the segment kernel is for unaligned windows only
     ({"IM2WIN_FP16_SEG": "s64p256"}, (1, 64, 10, 10, 64, 3, 3, 1), "f16"),
+    # four channels per lane need C_o % 4 == 0, two C_o > 1
+    ({"IM2WIN_FP16_DIRECT": "c64p64w8"}, (1, 64, 10, 10, 66, 3, 3, 1), "f16"),
+    ({"IM2WIN_FP16_DIRECT": "c32p16w8"}, (1, 64, 10, 10, 1, 3, 3, 1), "f16"),
     # 16-byte DMA windows need C_i % 4 == 0
     ({"IM2WIN_FP32_KERNEL": "p8c8l8s2k16"}, (1, 3, 10, 10, 64, 3, 3, 1), "f32"),
 ], ids=lambda x: x if isinstance(x, str) else "x".join(map(str, x)) if isinstance(x, tuple) else "+".join(x.values()))
@@ -114,6 +122,7 @@ def test_forced_mfma_tile_on_unaligned_layer_refused(monkeypatch):
     ("IM2WIN_FP16_KERNEL", "regs", "conv_fp16_kernel "),
     ("IM2WIN_FP16_TILE", "c128p128s1", "conv_fp16_pipe c128p128s1"),
     ("IM2WIN_FP16_COL", "k3c64p256t32s2", "conv_fp16_col k3c64p256t32s2"),
+    ("IM2WIN_FP16_DIRECT", "c64p64w4", "conv_fp16_direct c64p64w4"),
     ("IM2WIN_FP32_KERNEL", "regs", "conv_fp32_kernel m4n16f"),
     ("IM2WIN_FP32_KERNEL", "p4c12l8s2k16", "conv_fp32_dma p4c12l8s2k16"),
     ("IM2WIN_FP32_TILE", "m8n16f", "conv_fp32_kernel m8n16f"),
@@ -152,6 +161,18 @@ def test_persist_switch_names(monkeypatch):
         assert name((1, 64, 10, 10, 64, 3, 3, 1), "f16")
     monkeypatch.setenv("IM2WIN_FP16_PERSIST", "yes")
     assert status((1, 64, 10, 10, 64, 3, 3, 1), "f16") == EINVAL
+
+
+def test_direct_off(monkeypatch):
+    """IM2WIN_FP16_DIRECT=off: the planner does not consider the small-grid
+    kernel; another kernel may be forced beside it."""
+    sh = (1, 256, 16, 16, 256, 3, 3, 1)
+    assert name(sh, "f16") == "conv_fp16_direct c32p16w8"
+    monkeypatch.setenv("IM2WIN_FP16_DIRECT", "off")
+    assert name(sh, "f16") == "conv_fp16_pipe c64p64s4"
+    assert name((1, 36, 31, 45, 100, 3, 5, 2), "f16").startswith("conv_fp16_seg ")
+    monkeypatch.setenv("IM2WIN_FP16_TILE", "c128p128s2")
+    assert name(sh, "f16") == "conv_fp16_pipe c128p128s2"
 
 
 # The mini-batch path makes its plan for a full chunk and runs it on the
