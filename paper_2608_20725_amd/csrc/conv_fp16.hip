@@ -898,8 +898,8 @@ int pipe_split_default(const Shape &sh, int v)
     return v == pipe_find("c128p64s4") && sh.K >= 10240 && split_reserve_ways(sh) == 4 ? 4 : 1;
 }
 
-// Whether channel tiles of bm rows pad C_o by at most a fifth or so (the
-// padded rows are loaded and multiplied like the others).
+// Whether channel tiles of bm rows pad C_o by at most 30 % (the padded rows
+// are loaded and multiplied like the others).
 bool rows_fit(const Shape &sh, int64_t bm)
 {
     return round_up(sh.Co, bm) * 10 <= sh.Co * 13;
@@ -971,7 +971,15 @@ int pipe_default(const Shape &sh)
     // 616 vs 575 TFLOP/s, S4 670 vs 646; with fewer tiles it starves the
     // chip, with more the second round runs partly empty)
     if (tiles(256, 256) >= 128 && tiles(256, 256) <= 256 && sh.Co >= 256) {
-        if (rows_fit(sh, 256))
+        // C_o % 8 == 4: this tile writes 8-byte pieces from its registers, where
+        // the 128-row ones, staged through LDS, write single values to rows that
+        // are not 16-byte aligned.  Over 1000 such layers that it pads by more
+        // than 30 %, 128-row tiles / this one: to two of them per CU 1.19 under
+        // 200 taps, 1.02 at 400 to 700, 0.94 at 1000 to 1300, 0.80 from 3000; to
+        // three 1.34, 1.21, 1.12, 1.04; beyond 1.53 to 1.31 (3x3 16 -> 388
+        // dilated, 24367 pixels, 32.5 us and 23.5).  Other C_o, beyond three:
+        // long windows (1.00 to 1.13 from 2000 taps, 0.67 to 0.94 to 1600)
+        if (rows_fit(sh, 256) || (sh.Co % 8 == 4 && (t128 > 512 || sh.K < 800)) || (t128 > 768 && sh.K >= 2000))
             return pipe_find("c256p256s2w8");
         // C_o that it would pad by a third and more: 128-row tiles, with one
         // slot beyond two of them per CU (0.71 of its time to 512 tiles, 0.83 to

@@ -599,6 +599,7 @@ int col_default(const Shape &sh)
     // 240 at 87x87, 39 images, 46.1 vs 40.0; over 150 layers of 1.4 to 1.6 times
     // the row kernel's taps 1.10, of up to 1.35 times 0.98)
     const bool filled = sh.Kw * sh.Tp * 5 <= sh.K_pad * 7;
+    const bool wide_rows = rows_fit(sh, 256) || sh.Co % 8 == 4;
     if (fp16_single_slot_rows(sh) && !(sh.Kw == 3 && (sh.Co <= 128 || (sh.s == 1 && filled))))
         return -1;
     // C_o <= 64: 64 x 128 tiles, three workgroups per CU, more bytes in
@@ -624,10 +625,14 @@ int col_default(const Shape &sh)
     else if (sh.Kw == 7 && sh.Co <= 128)
         name = "k7c64p256t16s3";
     // eight-wave 256-channel tiles where they pad few channels (C_o = 320:
-    // 35.8 vs 27.7 us with 128-channel tiles)
-    else if (sh.Kw == 3 && sh.Co > 128 && rows_fit(sh, 256) && tiles(192) >= 160 && tiles(192) <= 256)
+    // 35.8 vs 27.7 us with 128-channel tiles) or C_o % 8 == 4: they write 8-byte
+    // pieces from their registers, where the smaller tiles, staged through LDS,
+    // write single values to rows that are not 16-byte aligned (3x3 24 -> 532,
+    // 15456 pixels, 24.1 and 33.2; over 400 such layers 0.81 of their time, 0.88
+    // from 2048 taps on)
+    else if (sh.Kw == 3 && sh.Co > 128 && wide_rows && tiles(192) >= 160 && tiles(192) <= 256)
         name = "k3c256p192t32s2w8";
-    else if (sh.Kw == 3 && sh.Co > 128 && rows_fit(sh, 256) && tiles(256) >= 160 && tiles(256) <= 256)
+    else if (sh.Kw == 3 && sh.Co > 128 && wide_rows && tiles(256) >= 160 && tiles(256) <= 256)
         name = "k3c256p256t32s2w8";
     // stride 1, more than one 128 x 128 tile per CU: each window column
     // loaded once for three filter columns leaves less L2 traffic than the

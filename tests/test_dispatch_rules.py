@@ -154,6 +154,23 @@ def test_segment_waves_on_short_strips(shape, want):
     # 256-row tiles only where C_o fills them
     ((31, 120, 53, 9, 520, 3, 3, 1), "c128p128s2"), ((23, 96, 19, 63, 289, 3, 3, 1), "c128p128s1"),
     ((128, 96, 24, 24, 256, 5, 5, 1), "c256p256s2w8"),
+    # or where 128-channel tiles, storing single values, are not far fewer rounds ahead
+    ((54, 40, 39, 37, 372, 2, 1, 2), "c256p256s2w8"),     # 23.8 with c128p128s2, 20.0
+    ((51, 80, 22, 22, 388, 5, 5, 1), "c256p256s2w8"), ((51, 80, 22, 22, 392, 5, 5, 1), "c128p128s1"),
+    ((51, 208, 22, 22, 388, 5, 5, 1), "c256p256s2w8"),
+    ((51, 40, 22, 22, 268, 5, 5, 1), "c128p128s2"), ((51, 24, 22, 22, 268, 5, 5, 1), "c256p256s2w8"),
+    ((78, 80, 22, 22, 392, 5, 5, 1), "c256p256s2w8"), ((78, 72, 22, 22, 392, 5, 5, 1), "c128p128s1"),
 ])
 def test_wide_row_tiles_need_filled_rows(shape, want):
     assert name(shape, "f16") == "conv_fp16_pipe " + want
+
+
+@pytest.mark.parametrize("shape,want", [
+    ((23, 24, 34, 23, 532, 3, 3, 1), "k3c256p192t32s2w8"),     # 33.2 with k3c128p128t32s2, 24.1
+    ((105, 16, 19, 19, 308, 3, 3, 1), "k3c256p256t32s2w8"),    # 29.8, 22.0
+    ((23, 376, 34, 23, 532, 3, 3, 1), "k3c256p192t32s2w8"),
+    ((105, 16, 24, 24, 188, 3, 3, 1), "k3c256p256t32s2w8"),
+    ((23, 24, 34, 23, 536, 3, 3, 1), "k3c128p128t32s2"), ((23, 24, 34, 23, 534, 3, 3, 1), "k3c128p128t32s2"),
+])
+def test_wide_column_tiles_on_8_byte_rows(shape, want):
+    assert name(shape, "f16") == "conv_fp16_col " + want
