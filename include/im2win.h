@@ -24,7 +24,8 @@
  *                     the kernels read past the last window without leaving
  *                     the buffer
  *     [pad_end, ...)  the filter repacked in window order (tap k = (v*K_h+u)*C_i+r)
- *                     and zero-padded, written by the conv call:
+ *                     and zero-padded, written by the conv call unless its
+ *                     kernel reads the caller's filter as it is:
  *                       fp16 / bf16: C_o_pad*K_w*T_pad 16-bit values, C_o_pad = round_up(C_o, 256),
  *                             T_pad = round_up(K_h*C_i, 64): tiles of TB taps, each
  *                             holding C_o_pad rows per slice, either one slice of
@@ -36,13 +37,21 @@
  *                             kernels; channels 2i and 2i+1 swapped in each row for the
  *                             LDS-staged kernel) and round_up(C_o, 128)*round_up(K, 32)
  *                             fp32 (conv_im2win_fp32_mfma)
+ *     then, fp16 / bf16, C_i a multiple of 8, C_o >= 128, at most 128 output
+ *     tiles of 128 x 128 and K > 1984: room for ks fp32 partial tiles per
+ *     output tile, ks <= 4 the largest that keeps the workspace within
+ *     conv_im2col_bytes (none where ks < 2, nor for some layers of 3- and
+ *     7-wide filters).  Windows of 10240 taps and more use it by default;
+ *     for the others it serves a forced IM2WIN_FP16_SPLIT only.
  *
  * Scope: one stride and one dilation for both axes; zero padding and dilation
  * through the *_padded / *_dilated calls below; no groups or bias.
  *
  * Ownership and threading: the caller allocates and frees every buffer; the
- * library allocates nothing and keeps no state except a once-filled per-device
- * record of whether the device is a gfx950.  Calls are reentrant.
+ * library allocates nothing and keeps no state except two per-device records:
+ * whether the device is a gfx950, and how many workgroups of one kernel family
+ * (conv_fp16_segw) fit it with the LDS of the last layer that ran each
+ * instance.  Calls are reentrant.
  *
  * Streams: every device call only enqueues work on `hip_stream` (a
  * hipStream_t; NULL is the null stream) and returns without synchronising.
@@ -57,7 +66,7 @@
  * library.  Kernel choice: each conv call picks its kernel from the layer's
  * shape (conv_im2win_kernel_name reports which).  Tuning variables in the
  * environment can force another, to measure kernels against each other:
- * IM2WIN_FP16_KERNEL (pipe | regs), IM2WIN_FP16_COL, IM2WIN_FP16_TILE,
+ * IM2WIN_FP16_KERNEL (pipe | regs | stem), IM2WIN_FP16_COL, IM2WIN_FP16_TILE,
  * IM2WIN_FP16_SEG, IM2WIN_FP16_DIRECT (a variant name | off), IM2WIN_FP32_KERNEL (a variant name | regs),
  * IM2WIN_FP32_TILE, IM2WIN_FP32_MFMA_TILE (variant names),
  * IM2WIN_TRANSFORM_ORDER and IM2WIN_TILE_ORDER (xcd | linear),

@@ -324,7 +324,8 @@ struct Tuning {
     bool direct_off;                   // the small-grid fp16 kernel is not considered
     bool col_persist;                  // column-staged fp16 kernel: persistent launch where it applies
     enum { kDefault = 0, kLinear = 1, kColumn = 2 };
-    int tap_order;  // kDefault: each kernel's own (column for the DMA fp32 kernel, linear for the others)
+    int tap_order;  // kDefault: each kernel's own (column for the DMA fp32 kernel and, where strided
+                    // windows overlap, the matrix-core one; linear for the others)
     int fp16_split; // K split of the row-per-pixel kernel: 0 (the planner's choice) or 1..kMaxSplit
 };
 int read_tuning(Tuning *t);

@@ -482,7 +482,8 @@ const DVariant *d_variants(int *n)
         d_variant<4, 4, 8, 1, 2, 16, 16, 4, 4>("p4c4l8s2k16t4"),
         d_variant<4, 4, 8, 1, 2, 16, 16, 8, 8>("p4c4l8s2k16t8w8"),
         d_variant<8, 8, 8, 1, 2, 16, 16, 8, 8>("p8c8l8s2k16t8w8"),
-        // the tap split with 4-byte window loads
+        // the tap split with 4-byte window loads; the second by name only
+        // (IM2WIN_FP32_KERNEL): no rule takes it
         d_variant<4, 4, 8, 1, 2, 16, 4, 4, 4>("p4c4l8s2k16g4t4"),
         d_variant<4, 8, 8, 1, 2, 16, 4, 4, 8>("p4c8l8s2k16g4t4w8"),
         // serialized rings of three of the above (check variants)

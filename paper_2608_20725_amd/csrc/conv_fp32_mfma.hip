@@ -212,8 +212,8 @@ __global__ __launch_bounds__(C::NT) void conv_fp32_mfma(M32Args a)
     // first load into it follows a barrier that follows every read of them):
     // an array of its own would take the 64 x 256 tile past half of the
     // 160 KiB LDS, one workgroup per CU instead of two (7x7 C=64 stride 2 at
-    // 224x224: 5204 us vs 4761 together
-    // with the column order of launch_conv_fp32_mfma).
+    // 224x224, 128 images: 5123 -> 4791 us together with the column order of
+    // launch_conv_fp32_mfma and the tile that mfma32_default takes).
     uint32_t *const rowoff = reinterpret_cast<uint32_t *>(C::NS > 3 ? r3 : C::NS > 2 ? r2 : r1);
 
     MTile<C> w;
@@ -530,10 +530,11 @@ hipError_t launch_conv_fp32_mfma(const Shape &sh, const Plan32 &plan, const Tuni
     a.wc = make_wincols(sh);
     a.div_Wo = make_fastdiv((uint32_t)sh.Wo);
     // Column order where windows overlap with a stride: 7x7 stride 2 C=64 at
-    // 224x224 is bound by re-reading its windows in linear order, 5405 us
-    // against 4761.  At stride 1 linear order is ahead: 3x3 C=64 at 56x56
-    // 253 against 266, 3x3 C=512 at 7x7 177 against 192, 3x3 64 -> 128 at
-    // 112x112 1770 against 1800.
+    // 224x224 is bound by re-reading its windows in linear order (64 x 256
+    // tiles 5410 us against 4970, the default 64 x 128 ones 5264 against 4791
+    // to 4960).  At stride 1 linear order is ahead: 3x3 C=64 at 56x56 253
+    // against 266, 3x3 C=512 at 7x7 177 against 192, 3x3 64 -> 128 at 112x112
+    // 1770 against 1800.
     const bool linear = t.tap_order == Tuning::kDefault ? sh.s == 1 || sh.Kw <= sh.s : t.tap_order == Tuning::kLinear;
     a.to = make_taporder(sh.Kw, sh.Kh, sh.Ci, (uint32_t)BK, linear, sh.s);
     const int64_t gx = (sh.P + v[pick].bn - 1) / v[pick].bn, gy = (sh.Co + v[pick].bm - 1) / v[pick].bm;
