@@ -57,18 +57,18 @@ METRIC = "conv TFLOPS (fp32 VALU, fp16 MFMA) + peak workspace bytes vs im2col"
 
 # HBM-side bytes per step moved by the conv kernels of the sweep, from
 # rocprofv3 FETCH_SIZE and WRITE_SIZE (KiB per dispatch) over the timed
-# dispatches of `bench.py --steps 20 --warmup 5`, each scaled by what the same
-# counter reads for a plain device copy of known size.  They hold only for the
+# dispatches of `bench.py --steps 4 --warmup 1 --no-extras`, each scaled by what
+# the same counter reads for a plain device copy of known size.  They hold only for the
 # kernel sources they were taken on (SHA-256 over KERNEL_SOURCES); after any
 # change to those sources the figure is reported as null until measured again.
 KERNEL_SOURCES = ("common.hpp", "epilogue16.hpp", "mfma16.hpp", "conv_fp32_dma.hip", "conv_fp32.hip",
                   "conv_fp32_stem.hip", "conv_fp16.hip", "conv_fp16_col.hip", "conv_fp16_seg.hip",
                   "conv_fp16_direct.hip", "conv_fp16_stem.hip")
 CONV_TRAFFIC = {
-    "source_sha256": "96305f1ad78cd6604670b1a3f1eb4601d2e68ee5078efc6ae9c597e2087e8093",
+    "source_sha256": "575528f37c557ba461924e83d39e460406f48971ce166b6cc1ce9f0a075b38b3",
     "workload": "sweep",
-    "f32": 16331651792,    # bytes per step, fetched + written
-    "f16": 6478535352,
+    "f32": 16342149744,    # bytes per step, fetched + written
+    "f16": 6483141736,
 }
 
 
