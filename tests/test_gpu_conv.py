@@ -477,3 +477,23 @@ def test_fp32_column_kernel(case, monkeypatch):
         monkeypatch.setenv("IM2WIN_FP32_COLS", name + "-serial")
         twin = Run(x, w, s, torch.float32)
         assert torch.equal(run.out.view(torch.int32), twin.out.view(torch.int32))
+
+
+# 256-channel tiles that write 8-byte pieces of rows that are not 16-byte
+# aligned: C_o = 4 mod 8, inside one tile and just past it, pixels off the tile
+@pytest.mark.parametrize("var,tile", [("IM2WIN_FP16_TILE", "c256p256s2w8"), ("IM2WIN_FP16_COL", "k3c256p192t32s2w8"),
+                                      ("IM2WIN_FP16_COL", "k3c256p256t32s2w8")])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16], ids=["f16", "bf16"])
+def test_wide_tiles_on_8_byte_rows(var, tile, dtype, monkeypatch):
+    monkeypatch.setenv(var, tile)
+    for shape in [(2, 8, 23, 17, 260, 3, 3, 1), (3, 16, 15, 19, 196, 3, 3, 1), (1, 24, 9, 21, 532, 3, 3, 1)]:
+        N, Ci, H, W, Co, Kh, Kw, s = shape
+        assert_kernel(shape, dtype, var, tile)
+        say("8-byte rows", tile, shape, dtype)
+        x, w = workloads.draw(N, Ci, H, W, Co, Kh, Kw, 41)
+        r = Run(x, w, s, dtype)
+        check_full(r, x, w)
+        r.check_out_guards()
+        xi, wi = workloads.draw(N, Ci, H, W, Co, Kh, Kw, 42, dist="int2")
+        ref = torch.from_numpy(oracle.conv(xi.double().numpy(), wi.double().numpy(), s)).to(dtype)
+        assert torch.equal(Run(xi, wi, s, dtype).out.cpu(), ref)
